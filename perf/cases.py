@@ -195,6 +195,7 @@ def work(case):
 
 def tolerance(case):
     # Against the same stack in fp64 (nothing rounded but weights, inputs and cached K/V) the outputs are off by 1.7e-3 after one tiny layer,
-    # which is the bf16 rounding of the output itself, and by 4.3e-3 to 6.9e-3 after 4 to 8 wide layers (bf16 K/V, queries and layer outputs);
-    # the worst element by 0.032 of the result's rms.
-    return {"rel": 1e-2, "max": 0.1}
+    # which is the bf16 rounding of the output itself, and by 4.3e-3 to 6.9e-3 after 4 to 8 wide layers (bf16 K/V, queries and layer outputs,
+    # carried on by every layer behind them); the worst element by 0.032 of the result's rms.  With the attention's sums in another order,
+    # everything else the same, the outputs move by 2.2e-3 (2 layers) to 8.2e-3 (8 layers, one row).
+    return {"rel": 1e-2 if case["layers"] <= 2 else 2e-2, "max": 0.12}
