@@ -1,8 +1,8 @@
 // Paged grouped-query decode attention (Sec. 2.3: one query token per request against all of its cached keys; a
 // memory-bound sweep over the KV cache), split over the context, plus the merge of the split results.
 //
-// Work item = (request, kv head, span of kSpan keys), one wavefront each, independent of every other work item.
-// The span boundaries depend on the context length only, so the reduction order is the same on any CU share.
+// Work item = (request, kv head, span of `span` keys), one wavefront each, independent of every other work item.
+// The span is a function of the batch alone (plan_span), so the reduction order is the same on any CU share.
 // The wavefront serves all G query heads of its kv head at once, so every K/V byte is fetched once per kv head.
 // K and V pages are read straight from global memory into MFMA operand registers: the private page layouts make
 // each load instruction cover contiguous runs of memory with 16 bytes per lane, and no LDS is needed because
@@ -18,13 +18,35 @@
 
 namespace nexus {
 
-constexpr int kSpan = 256;  // keys per work item (16 pages)
+// Keys per work item.  A wavefront pays a fixed chain of latencies (context length, page ids, first pages: 3 us on an idle
+// chip, 7 us in the queue of a loaded one) and its partial result is written and merged, so a span is as long as still
+// leaves several rounds of the chip's 2048 wavefronts to balance ragged contexts: 256 requests with contexts up to 8192,
+// spans of 256 / 1024 keys: 815 / 772 us and the merge 10.8 / 6.5.  A batch too small to fill the chip takes the
+// shortest spans that still do not outnumber its SIMDs (one request of 800 keys, spans of 256 / 64: 8.5 / 5.6 us), unless
+// one span of 256 holds every context: then there is nothing to merge.
+constexpr int kSpanMin = 64, kSpanMax = 1024;  // up to 64 pages: a wavefront keeps its page ids one per lane
+constexpr int kSpanItems = 8192, kSpanItemsSmall = 1024;
+__host__ __device__ __forceinline__ int plan_span(int n_reqs, int n_kv_heads, int max_ctx) {
+    auto items = [&](int span) { return (long)n_reqs * n_kv_heads * ((max_ctx + span - 1) / span); };
+    int span = kSpanMax;
+    while (span > 256 && items(span) < kSpanItems) span >>= 1;
+    if (max_ctx > 256)
+        while (span > kSpanMin && items(span >> 1) <= kSpanItemsSmall) span >>= 1;
+    return span;
+}
+// Upper bound of the items of any batch of up to n_reqs requests with contexts up to max_ctx: a span below the largest
+// means that twice that span gave fewer than kSpanItems items.
+inline size_t max_span_items(int n_reqs, int n_kv_heads, int max_ctx) {
+    const size_t pairs = (size_t)n_reqs * n_kv_heads, at_max = pairs * ((max_ctx + kSpanMax - 1) / kSpanMax);
+    const size_t at_min = pairs * ((max_ctx + kSpanMin - 1) / kSpanMin), bound = 2 * (size_t)kSpanItems;
+    return at_max > bound ? at_max : bound < at_min ? bound : at_min;
+}
 constexpr int kDecWaves = 1;  // work items (wavefronts) per workgroup
 
 struct AttnDecodeArgs {
     const bf16_t *q;  // row-major [B][Hq*hd], rotated
     const int32_t *ctx_len, *page_table;
-    int n_reqs, max_pages, max_spans;
+    int n_reqs, max_pages, span, max_spans;  // max_spans = ceil(largest context / span); 1: outputs go straight to `out`
     const bf16_t *k_pool, *v_pool;
     int n_pages, Hq, Hkv;
     float scale_log2e;
@@ -56,17 +78,17 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void attn_decode_kernel(AttnDeco
     const int j = (wi % per_span) / a.Hkv;
     const int kvh = wi % a.Hkv;
     const int len = a.ctx_len[j] + 1;
-    const int k_begin = span * kSpan;
+    const int k_begin = span * a.span;
     if (k_begin >= len) return;
-    const int k_end = min(len, k_begin + kSpan);
+    const int k_end = min(len, k_begin + a.span);
     const int col = lane & 15, g4 = lane >> 4;
 
-    // The span's 16 page ids, one per lane, fetched once: no key/value load waits on a page-table read.  Ids that
+    // The span's page ids (at most 64), one per lane, fetched once: no key/value load waits on a page-table read.  Ids that
     // are out of range or belong to pages past the end of the context are replaced by page 0: every load below
     // then has a valid address and no branch, and what it fetches for such a page is masked out.
     int my_page = 0;
     {
-        const int lp = (k_begin >> 4) + col;
+        const int lp = (k_begin >> 4) + lane;
         if (lp * 16 < k_end && lp < a.max_pages) my_page = a.page_table[(size_t)j * a.max_pages + lp];
         if ((unsigned)my_page >= (unsigned)a.n_pages) my_page = 0;
     }
@@ -197,6 +219,14 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void attn_decode_kernel(AttnDeco
     // stored normalised (an average of value rows, inside half's range whenever the values are) and in half: half
     // the bytes of an fp32 partial, at a rounding 4x finer than the bf16 the values came in; a span is never empty
     const float inv_l = 1.0f / l_run;
+    if (a.max_spans == 1) {  // nothing to merge: the output row itself, half, P32
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            uint2 o = {packh2(o_acc[i][0] * inv_l, o_acc[i][1] * inv_l), packh2(o_acc[i][2] * inv_l, o_acc[i][3] * inv_l)};
+            *(uint2 *)(a.out + p32_offset(a.out_row0 + j, (kvh * G + col) * HD + 16 * i + 4 * g4, a.Hq * HD)) = o;
+        }
+        return;
+    }
     f16_t *po = a.part_o + (item * G + col) * HD;
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
@@ -216,7 +246,7 @@ __global__ __launch_bounds__(64) void attn_merge_kernel(AttnDecodeArgs a) {
     const int j = blockIdx.x / a.Hq, hq = blockIdx.x % a.Hq;
     const int kvh = hq / G, col = hq % G, lane = threadIdx.x;
     const int len = a.ctx_len[j] + 1;
-    const int n_spans = (len + kSpan - 1) / kSpan;
+    const int n_spans = (len + a.span - 1) / a.span;
     const size_t item0 = ((size_t)j * a.Hkv + kvh) * a.max_spans;
     constexpr int EPL = HD / 64;
     float acc[EPL], m = -INFINITY, denom = 0.f;

@@ -38,7 +38,7 @@ using namespace nexus;
 // Workspace of nexus_decode_step_noalloc: device memory that exists from the moment the library is loaded, so the
 // call allocates nothing.  One copy per GPU, shared by every context on that GPU, held until the process ends.  In
 // host code the array's name is only a handle: its device address comes from hipGetSymbolAddress, once per device.
-constexpr size_t kScratchBytes = (size_t)32 << 20;
+constexpr size_t kScratchBytes = (size_t)40 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 static unsigned char *g_scratch_ptr[kMaxDevices] = {};
@@ -81,7 +81,6 @@ struct PhaseWs {
     float *partial = nullptr;
     size_t partial_elems = 0;
     float *part_o = nullptr, *part_ml = nullptr;  // decode attention split results
-    int max_spans = 0;
     int q_rows = 0;
 };
 
@@ -520,7 +519,7 @@ static int launch_attn_decode(const PhaseRun &r, const AttnDecodeArgs &a) {
             hipLaunchKernelGGL((attn_decode_kernel<HD, GG>), grid, dim3(64 * kDecWaves), 0, r.s, a);         \
         }                                                                                         \
         HIP_TRY(hipGetLastError());                                                               \
-        {                                                                                         \
+        if (a.max_spans > 1) {                                                                    \
             Tracer tr(c, r.phase, NEXUS_K_ATTN_MERGE, r.s);                                       \
             hipLaunchKernelGGL((attn_merge_kernel<HD, GG>), mgrid, dim3(64), 0, r.s, a);          \
         }                                                                                         \
@@ -597,7 +596,7 @@ static int run_layer(const PhaseRun &r, int layer, const bf16_t *x_in, bf16_t *y
             const int lead = r.pb->n_reqs - r.fused_decode;
             AttnDecodeArgs d{};
             d.q = ws.q, d.ctx_len = r.pb->prefix_len + lead, d.page_table = r.pb->page_table + (size_t)lead * r.pb->max_pages;
-            d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.max_spans = (r.fused_max_ctx + kSpan - 1) / kSpan;
+            d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.span = plan_span(d.n_reqs, m.n_kv_heads, r.fused_max_ctx), d.max_spans = (r.fused_max_ctx + d.span - 1) / d.span;
             d.k_pool = k_pool, d.v_pool = v_pool, d.n_pages = r.kv->n_pages, d.Hq = m.n_q_heads, d.Hkv = m.n_kv_heads;
             d.scale_log2e = scale_log2e, d.part_o = (f16_t *)c->ws[NEXUS_PHASE_DECODE].part_o, d.part_ml = c->ws[NEXUS_PHASE_DECODE].part_ml;
             d.out = ws.attn, d.lead_cu = r.pb->cu_chunk, d.n_lead = lead, d.out_row0 = r.pb->n_tokens - r.fused_decode;
@@ -606,7 +605,7 @@ static int run_layer(const PhaseRun &r, int layer, const bf16_t *x_in, bf16_t *y
     } else {
         AttnDecodeArgs a{};
         a.q = ws.q, a.ctx_len = r.db->ctx_len, a.page_table = r.db->page_table, a.n_reqs = r.db->n_reqs;
-        a.max_pages = r.db->max_pages, a.max_spans = (r.db->max_ctx + kSpan - 1) / kSpan;
+        a.max_pages = r.db->max_pages, a.span = plan_span(a.n_reqs, m.n_kv_heads, r.db->max_ctx), a.max_spans = (r.db->max_ctx + a.span - 1) / a.span;
         a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
         a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.out = ws.attn;
         NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, a) : launch_attn_decode<64>(r, a));
@@ -848,9 +847,7 @@ static int alloc_phase_ws(nexus_ctx *c, int phase, int maxT, int max_reqs) {
         NX_TRY(dev_alloc(&w.part_ml, items * 2, false));
     } else {
         NX_TRY(dev_alloc(&w.q, (size_t)maxT * c->q_dim, true));
-        w.max_spans = (c->lim.max_positions + kSpan - 1) / kSpan;
-        const int G = m.n_q_heads / m.n_kv_heads;
-        const size_t items = (size_t)maxT * m.n_kv_heads * w.max_spans * G;
+        const size_t items = max_span_items(maxT, m.n_kv_heads, c->lim.max_positions) * (m.n_q_heads / m.n_kv_heads);
         NX_TRY(dev_alloc(&w.part_o, (items * m.head_dim + 1) / 2, false));  // half elements
         NX_TRY(dev_alloc(&w.part_ml, items * 2, false));
     }
@@ -1194,8 +1191,8 @@ static size_t carve_decode_ws(const nexus_ctx *c, int T, int max_ctx, bool multi
         ws.xbuf[1] = (bf16_t *)take((size_t)T * m.hidden * 2);
     }
     *zero_bytes = off;
-    ws.max_spans = (max_ctx + kSpan - 1) / kSpan;
-    const size_t items = (size_t)T * m.n_q_heads * ws.max_spans;  // (request, kv head, span) x the G heads of the kv head
+    const int span = plan_span(T, m.n_kv_heads, max_ctx);
+    const size_t items = (size_t)T * m.n_q_heads * ((max_ctx + span - 1) / span);  // (request, kv head, span) x the G heads of the kv head
     ws.part_o = (float *)take(items * m.head_dim * 2);  // half elements
     ws.part_ml = (float *)take(items * 2 * 4);
     size_t pe = 0;
