@@ -243,8 +243,8 @@ int nexus_decode_step(nexus_ctx *ctx, int layer_begin, int layer_end, const nexu
  * The array is 40 MiB per GPU, exists from library load to process exit and is shared by every context on that
  * GPU: calls that overlap in time on one GPU race on it (calls of one context are ordered by the decode stream).
  * A step whose workspace does not fit fails with NEXUS_ESHAPE before anything is launched: the need grows with
- * n_reqs x (the split-K partial sums of the widest split projection + the attention partials of the contexts'
- * spans); a hidden-4096 GQA layer takes about 23 MB for 64 requests with contexts up to 4096 and does not fit
+ * n_reqs x (the split-K partial sums of the widest split projection + the attention's partial
+ * results); a hidden-4096 GQA layer takes about 23 MB for 64 requests with contexts up to 4096 and does not fit
  * 256 requests with contexts up to 8192.
  * nexus_debug_fetch does not see this call's buffers.
  */

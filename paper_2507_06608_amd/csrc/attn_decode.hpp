@@ -1,57 +1,51 @@
 // Paged grouped-query decode attention (Sec. 2.3: one query token per request against all of its cached keys; a
 // memory-bound sweep over the KV cache), split over the context, plus the merge of the split results.
 //
-// Work item = (request, kv head, span of `span` keys), one wavefront each, independent of every other work item.
-// The span is a function of the batch alone (plan_span), so the reduction order is the same on any CU share.
-// The wavefront serves all G query heads of its kv head at once, so every K/V byte is fetched once per kv head.
-// K and V pages are read straight from global memory into MFMA operand registers: the private page layouts make
-// each load instruction cover contiguous runs of memory with 16 bytes per lane, and no LDS is needed because
-// nothing is shared between wavefronts.  The products run on v_mfma_f32_16x16x32_bf16 with the G query heads
-// padded to the 16 columns of the tile; on this memory-bound sweep the matrix unit is otherwise idle, while the
-// same work on the vector ALUs would cost about G+1 instructions per KV element and bind before HBM does once
-// the phase only owns a fraction of the CUs.  As in the prefill kernel the transposed orientation
-// (S^T = K Q^T, O^T = V^T P^T) keeps softmax statistics per lane and lets the S^T accumulators serve directly as
-// the P^T operand.  The loop is kept lean on purpose (no per-load predicates, raw v_exp_f32): with a dozen VALU
-// instructions per key the sweep would be instruction-bound, not memory-bound.
+// The keys of the batch, laid out request by request, kv head by kv head, are cut into runs of equal length (in pairs
+// of pages, 32 keys) and every run is one wavefront's, whatever requests and heads it touches: ragged contexts leave
+// no wavefront with more to do than another.  The cut is a function of the batch alone, so the reduction order is the
+// same on any CU share.  The wavefront serves all G query heads of its kv head at once, so every K/V byte is fetched
+// once per kv head.  K and V pages are read straight from global memory into MFMA operand registers: the private page
+// layouts make each load instruction cover contiguous runs of memory with 16 bytes per lane, and no LDS is needed because
+// nothing is shared between wavefronts.  S^T = K Q^T and O^T += V^T P^T with the 16x16x32 bf16 MFMA: one column per
+// query head, softmax running max / sum kept per column, and the score registers of two consecutive 16-row tiles
+// are exactly the 8 probabilities the matching V^T operand needs (no transpose between the products).
+//
+// Queries are the rotated bf16 rows written by the rotary kernel; the new token's K/V is already in the pools
+// (appended by the same kernel), so a request with c cached tokens attends to c+1 keys.
 #pragma once
 #include "common.hpp"
 
 namespace nexus {
 
-// Keys per work item.  A wavefront pays a fixed chain of latencies (context length, page ids, first pages: 3 us on an idle
-// chip, 7 us in the queue of a loaded one) and its partial result is written and merged, so a span is as long as still
-// leaves several rounds of the chip's 2048 wavefronts to balance ragged contexts: 256 requests with contexts up to 8192,
-// spans of 256 / 1024 keys: 815 / 772 us and the merge 10.8 / 6.5.  A batch too small to fill the chip takes the
-// shortest spans that still do not outnumber its SIMDs (one request of 800 keys, spans of 256 / 64: 8.5 / 5.6 us), unless
-// one span of 256 holds every context: then there is nothing to merge.
-constexpr int kSpanMin = 64, kSpanMax = 1024;  // up to 64 pages: a wavefront keeps its page ids one per lane
-constexpr int kSpanItems = 8192, kSpanItemsSmall = 1024;
-__host__ __device__ __forceinline__ int plan_span(int n_reqs, int n_kv_heads, int max_ctx) {
-    auto items = [&](int span) { return (long)n_reqs * n_kv_heads * ((max_ctx + span - 1) / span); };
-    int span = kSpanMax;
-    while (span > 256 && items(span) < kSpanItems) span >>= 1;
-    if (max_ctx > 256)
-        while (span > kSpanMin && items(span >> 1) <= kSpanItemsSmall) span >>= 1;
-    return span;
+// Wavefronts the keys are dealt to: one per SIMD of the chip, so that all run at once and end together.  A wavefront
+// pays a fixed chain of latencies (context lengths, page ids, first pages: 3 us on an idle chip, 7 us in the queue of a
+// loaded one) per stretch of one request's keys, and a partial result per stretch is written and merged; runs of equal
+// length have few of either.  256 requests with contexts up to 8192: fixed spans of 256 / 1024 keys 815 / 764 us, 512 /
+// 1024 / 2048 / 4096 equal runs 757 / 733 / 746 / 751 us (6.5 TB/s; plain reads of such a size reach 7.0); 64 requests up
+// to 4096 on 64 CUs next to a prefill phase 231 -> 212.  Three or four pairs in flight per wavefront instead of two gain
+// nothing.  A run is at least two pairs long (one request of 800 keys: spans of 256 keys took 8.5 us, runs of 64 take 6.4),
+// and where 256 keys hold every context a wavefront takes one whole (request, kv head): there is then nothing to merge.
+constexpr int kDecWorkers = 1024, kDecMinPairs = 2, kDecWholeCtx = 256;
+inline int decode_grid(int n_reqs, int n_kv_heads, int max_ctx) {
+    const long seqs = (long)n_reqs * n_kv_heads;
+    if (max_ctx <= kDecWholeCtx) return (int)seqs;
+    const long runs = (seqs * ((max_ctx + 31) / 32) + kDecMinPairs - 1) / kDecMinPairs;
+    return (int)(runs < kDecWorkers ? runs : kDecWorkers);
 }
-// Upper bound of the items of any batch of up to n_reqs requests with contexts up to max_ctx: a span below the largest
-// means that twice that span gave fewer than kSpanItems items.
-inline size_t max_span_items(int n_reqs, int n_kv_heads, int max_ctx) {
-    const size_t pairs = (size_t)n_reqs * n_kv_heads, at_max = pairs * ((max_ctx + kSpanMax - 1) / kSpanMax);
-    const size_t at_min = pairs * ((max_ctx + kSpanMin - 1) / kSpanMin), bound = 2 * (size_t)kSpanItems;
-    return at_max > bound ? at_max : bound < at_min ? bound : at_min;
-}
-constexpr int kDecWaves = 1;  // work items (wavefronts) per workgroup
+// Partial results of a batch: each is the first of its run or the first of its (request, kv head).
+inline size_t decode_part_slots(int n_reqs, int n_kv_heads) { return (size_t)kDecWorkers + (size_t)n_reqs * n_kv_heads; }
 
 struct AttnDecodeArgs {
     const bf16_t *q;  // row-major [B][Hq*hd], rotated
     const int32_t *ctx_len, *page_table;
-    int n_reqs, max_pages, span, max_spans;  // max_spans = ceil(largest context / span); 1: outputs go straight to `out`
+    int n_reqs, max_pages, max_ctx;  // max_ctx <= kDecWholeCtx: outputs go straight to `out`
+    int2 *seq_parts;  // [B][Hkv] (run of the first key, number of partial results), written by the wavefront that holds the first key
     const bf16_t *k_pool, *v_pool;
     int n_pages, Hq, Hkv;
     float scale_log2e;
-    f16_t *part_o;   // [B][Hkv][max_spans][G][hd]: each span's output normalised by its own sum, half
-    float *part_ml;  // [B][Hkv][max_spans][G][2]  (running max in the log2 domain, sum)
+    f16_t *part_o;   // [run + (request, kv head)][G][hd]: each stretch's output normalised by its own sum, half
+    float *part_ml;  // [run + (request, kv head)][G][2]  (running max in the log2 domain, sum)
     f16_t *out;      // merge output: half, P32 [B rows][Hq*hd]
     // Decode requests riding in a chunked-prefill batch (the fused single-batch step): their queries sit in the
     // prefill layout -- P32, every request on a 32-row boundary, request j of the decode part in the row tile that
@@ -61,44 +55,98 @@ struct AttnDecodeArgs {
     int n_lead, out_row0;
 };
 
+// Keys of request j (contexts past the hint are cut: the hint bounds the work, the page table its reads), and their pairs.
+__device__ __forceinline__ int decode_len(const AttnDecodeArgs &a, int j) {
+    const int c = a.ctx_len[min(j, a.n_reqs - 1)];  // no branch around the load: the four of a lane are in flight together
+    return j < a.n_reqs ? max(0, min(c + 1, a.max_ctx)) : 0;
+}
+__device__ __forceinline__ int decode_pairs(int len) { return (len + 31) >> 5; }
+
+// Inclusive sum over the lanes of a wavefront, by lane moves of the vector ALU (no trip through LDS).
+__device__ __forceinline__ int wave_inclusive_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);  // row_shr:1, 2, 4, 8: sums inside the rows of 16 lanes
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, true);  // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, true);  // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
 template <int HD, int G>
-__global__ __launch_bounds__(kDecWaves * 64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
+__global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
     constexpr int KK = HD / 32;   // k-steps of QK^T
     constexpr int RT = HD / 16;   // 16-row tiles of O^T
     constexpr int BLK = kPage * HD;  // elements per (page, kv head) block
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    // Work items are numbered span-major: workgroups are dealt to the 8 XCDs round-robin, and with the span index
-    // running fastest each XCD would always serve the same span positions -- the first spans, which every
-    // request has, on some XCDs and the rarely present last spans on others (measured: 1.4x the time of a
-    // balanced launch on a third of the chip).  Span-major, each span's (request, kv head) items spread evenly.
-    const int wi = blockIdx.x * kDecWaves + w;
-    const int per_span = a.n_reqs * a.Hkv;
-    const int span = wi / per_span;
-    if (span >= a.max_spans) return;
-    const int j = (wi % per_span) / a.Hkv;
-    const int kvh = wi % a.Hkv;
-    const int len = a.ctx_len[j] + 1;
-    const int k_begin = span * a.span;
-    if (k_begin >= len) return;
-    const int k_end = min(len, k_begin + a.span);
+    const int lane = threadIdx.x & 63;
     const int col = lane & 15, g4 = lane >> 4;
+    const int w = blockIdx.x;
 
-    // The span's page ids (at most 64), one per lane, fetched once: no key/value load waits on a page-table read.  Ids that
-    // are out of range or belong to pages past the end of the context are replaced by page 0: every load below
-    // then has a valid address and no branch, and what it fetches for such a page is masked out.
-    int my_page = 0;
-    {
-        const int lp = (k_begin >> 4) + lane;
-        if (lp * 16 < k_end && lp < a.max_pages) my_page = a.page_table[(size_t)j * a.max_pages + lp];
-        if ((unsigned)my_page >= (unsigned)a.n_pages) my_page = 0;
+    // This wavefront's run: pairs [run_begin, run_begin + todo) of the batch's pairs in (request, kv head) order.  A lane
+    // counts the pairs of 4 consecutive requests, a wavefront scan places 256.
+    int j = 0, kvh = 0, pair = 0, todo = 0, per = 1, run_begin = 0, len = 0;
+    const bool whole = a.max_ctx <= kDecWholeCtx;
+    if (whole) {
+        j = w / a.Hkv, kvh = w % a.Hkv;
+        len = decode_len(a, j);
+        todo = decode_pairs(len);
+        if (todo == 0) return;
+    } else {
+        int lens[4], mine = 0, incl = 0, total = 0;
+        auto scan = [&](int base) {  // incl: pairs per kv head of the requests base .. base + 4 lane + 3
+#pragma unroll
+            for (int e = 0; e < 4; ++e) lens[e] = decode_len(a, base + 4 * lane + e);
+            mine = decode_pairs(lens[0]) + decode_pairs(lens[1]) + decode_pairs(lens[2]) + decode_pairs(lens[3]);
+            incl = wave_inclusive_sum(mine);
+            return __builtin_amdgcn_readlane(incl, 63);
+        };
+        for (int base = 0; base < a.n_reqs; base += 256) total += scan(base);
+        total *= a.Hkv;
+        per = max(kDecMinPairs, (total + kDecWorkers - 1) / kDecWorkers);
+        run_begin = w * per;
+        if (run_begin >= total) return;
+        todo = min(per, total - run_begin);
+        int before = 0, base = 0;  // pairs of the requests before `base`, then before j
+        if (a.n_reqs > 256) {
+            int t;
+            while (run_begin >= before + (t = scan(base)) * a.Hkv) before += t * a.Hkv, base += 256;
+        }
+        const int hit = __builtin_ctzll(__builtin_amdgcn_ballot_w64(run_begin < before + incl * a.Hkv));
+        before += __builtin_amdgcn_readlane(incl - mine, hit) * a.Hkv;
+        j = base + 4 * hit;
+        len = __builtin_amdgcn_readlane(lens[0], hit);
+#pragma unroll
+        for (int e = 1; e < 4; ++e) {
+            const int c = decode_pairs(len) * a.Hkv;
+            if (j == base + 4 * hit + e - 1 && run_begin >= before + c) before += c, ++j, len = __builtin_amdgcn_readlane(lens[e], hit);
+        }
+        const int np = decode_pairs(len), rest = run_begin - before;
+        kvh = rest / np, pair = rest % np;
     }
+    j = __builtin_amdgcn_readfirstlane(j), kvh = __builtin_amdgcn_readfirstlane(kvh), len = __builtin_amdgcn_readfirstlane(len);
+    pair = __builtin_amdgcn_readfirstlane(pair), todo = __builtin_amdgcn_readfirstlane(todo);
 
-    int q_row = 0;
-    if (a.lead_cu) {
-        int tiles = j;
-        for (int i = 0; i < a.n_lead; ++i) tiles += (a.lead_cu[i + 1] - a.lead_cu[i] + 31) >> 5;
-        q_row = tiles * 32;
-    }
+    const int half_off = (col & 7) * 8 + g4 * 128;  // elements: slot (col % 8) of a tile's half, k-group g4
+    int lead_tiles = 0;
+    if (a.lead_cu)
+        for (int i = 0; i < a.n_lead; ++i) lead_tiles += (a.lead_cu[i + 1] - a.lead_cu[i] + 31) >> 5;
+
+    // one stretch of a (request, kv head) after another
+    for (int at = run_begin; todo > 0;) {
+    const int np = decode_pairs(len), n_pairs = min(todo, np - pair);
+    if (n_pairs > 0) {
+    // Page ids, 64 at a time, one per lane: no key/value load waits on a page-table read.  Ids that are out of range or
+    // belong to pages past the end of the context are replaced by page 0: every load below then has a valid address and
+    // no branch, and what it fetches for such a page is masked out.
+    auto page_ids = [&](int lp0) {
+        const int lp = lp0 + lane;
+        int id = 0;
+        if (lp * 16 < len && lp < a.max_pages) id = a.page_table[(size_t)j * a.max_pages + lp];
+        return (unsigned)id < (unsigned)a.n_pages ? id : 0;
+    };
+    int my_page = page_ids(2 * pair);
+
+    const int q_row = (lead_tiles + j) * 32;
     bf16x8 qf[KK];
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) {
@@ -123,9 +171,8 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void attn_decode_kernel(AttnDeco
     struct PairRegs {
         u32x4 k1[KK], k2[KK], v[RT];
     };
-    const int half_off = (col & 7) * 8 + g4 * 128;  // elements: slot (col % 8) of a tile's half, k-group g4
-    auto load_pair = [&](PairRegs &r, int pp) {
-        const int pageA = __builtin_amdgcn_readlane(my_page, 2 * pp), pageB = __builtin_amdgcn_readlane(my_page, 2 * pp + 1);
+    auto load_pair = [&](PairRegs &r, int ids, int pp) {  // pair pp of the 32 whose page ids are given
+        const int pageA = __builtin_amdgcn_readlane(ids, 2 * pp), pageB = __builtin_amdgcn_readlane(ids, 2 * pp + 1);
         // K operand row (lane % 16): rows 0..7 from page A, 8..15 from page B
         const bf16_t *kp = a.k_pool + ((size_t)(col < 8 ? pageA : pageB) * a.Hkv + kvh) * BLK + half_off;
         // V operand: lane group g4 reads page g4 / 2, token group g4 % 2, hd rows 16 i + col
@@ -140,7 +187,7 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void attn_decode_kernel(AttnDeco
 #pragma unroll
         for (int i = 0; i < RT; ++i) r.v[i] = __builtin_nontemporal_load((const u32x4 *)(vp + i * 128));
     };
-    auto compute_pair = [&](PairRegs &r, int pp) {
+    auto compute_pair = [&](PairRegs &r, int p) {  // pair p of the request
         f32x4 s1 = {0, 0, 0, 0}, s2 = {0, 0, 0, 0};
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
@@ -148,30 +195,30 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void attn_decode_kernel(AttnDeco
             s2 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(bf16x8 *)&r.k2[kk], qf[kk], s2, 0, 0, 0);
         }
         // register e of s1 is key key0 + e, of s2 key key0 + 4 + e
-        const int key0 = k_begin + 32 * pp + 16 * (g4 >> 1) + 8 * (g4 & 1);
+        const int key0 = 32 * p + 16 * (g4 >> 1) + 8 * (g4 & 1);
         float sv[8];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             sv[e] = s1[e] * a.scale_log2e;
             sv[4 + e] = s2[e] * a.scale_log2e;
         }
-        const bool tail = k_begin + 32 * pp + 32 > k_end;  // uniform: only the last pair of a context
+        const bool tail = 32 * p + 32 > len;  // uniform: only the last pair of a context
         if (tail) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sv[e] = key0 + e < k_end ? sv[e] : -INFINITY;
+            for (int e = 0; e < 8; ++e) sv[e] = key0 + e < len ? sv[e] : -INFINITY;
             // values past the end of the context may hold anything; their weight is 0 but 0 * NaN is not
 #pragma unroll
             for (int i = 0; i < RT; ++i)
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
-                    if (key0 + e >= k_end) r.v[i][e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
+                    if (key0 + e >= len) r.v[i][e >> 1] &= (e & 1) ? 0x0000ffffu : 0xffff0000u;
         }
         float mx = m_run;
 #pragma unroll
         for (int e = 0; e < 8; ++e) mx = fmaxf(mx, sv[e]);
         mx = fmaxf(mx, __shfl_xor(mx, 16));
         mx = fmaxf(mx, __shfl_xor(mx, 32));
-        // the first key of the span is always valid, so mx is finite
+        // the first key of a pair is always valid, so mx is finite
         const float alpha = __builtin_amdgcn_exp2f(m_run - mx);
         m_run = mx;
         float rs = 0.f;
@@ -194,60 +241,84 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void attn_decode_kernel(AttnDeco
     // Two register sets: the loads of the next pair are in flight while the current pair is computed.  The steady
     // state loop has no branch around a prefetch: with one, the paths with and without the extra loads in flight
     // merge, and the compiler can only wait as if they had not been issued, i.e. for the prefetch itself.
-    const int n_pairs = (k_end - k_begin + 31) >> 5;
     PairRegs r0, r1;
-    load_pair(r0, 0);
-    int pp = 0;
-    for (; pp + 2 < n_pairs; pp += 2) {
-        load_pair(r1, pp + 1);
-        compute_pair(r0, pp);
-        load_pair(r0, pp + 2);
-        compute_pair(r1, pp + 1);
+    load_pair(r0, my_page, 0);
+    int done = 0;  // pairs of this stretch behind the window of 32 whose page ids are in my_page
+    for (; n_pairs - done > 32; done += 32) {
+        const int next_page = page_ids(2 * (pair + done + 32));
+        for (int pp = 0; pp < 30; pp += 2) {
+            load_pair(r1, my_page, pp + 1);
+            compute_pair(r0, pair + done + pp);
+            load_pair(r0, my_page, pp + 2);
+            compute_pair(r1, pair + done + pp + 1);
+        }
+        load_pair(r1, my_page, 31);
+        compute_pair(r0, pair + done + 30);
+        load_pair(r0, next_page, 0);
+        compute_pair(r1, pair + done + 31);
+        my_page = next_page;
     }
-    if (pp + 1 < n_pairs) {
-        load_pair(r1, pp + 1);
-        compute_pair(r0, pp);
-        compute_pair(r1, pp + 1);
-    } else {
-        compute_pair(r0, pp);
+    {
+        const int left = n_pairs - done, p0 = pair + done;
+        int pp = 0;
+        for (; pp + 2 < left; pp += 2) {
+            load_pair(r1, my_page, pp + 1);
+            compute_pair(r0, p0 + pp);
+            load_pair(r0, my_page, pp + 2);
+            compute_pair(r1, p0 + pp + 1);
+        }
+        if (pp + 1 < left) {
+            load_pair(r1, my_page, pp + 1);
+            compute_pair(r0, p0 + pp);
+            compute_pair(r1, p0 + pp + 1);
+        } else {
+            compute_pair(r0, p0 + pp);
+        }
     }
     l_run += __shfl_xor(l_run, 16);
     l_run += __shfl_xor(l_run, 32);
-    if (col >= G) return;
-    // register e of o_acc[i] is hd = 16 i + 4 g4 + e
-    const size_t item = ((size_t)j * a.Hkv + kvh) * a.max_spans + span;
-    // stored normalised (an average of value rows, inside half's range whenever the values are) and in half: half
-    // the bytes of an fp32 partial, at a rounding 4x finer than the bf16 the values came in; a span is never empty
+    // register e of o_acc[i] is hd = 16 i + 4 g4 + e.  Stored normalised (an average of value rows, inside half's range
+    // whenever the values are) and in half: half the bytes of an fp32 partial, at a rounding 4x finer than the bf16 the
+    // values came in; a stretch is never empty
+    const int seq = j * a.Hkv + kvh;
     const float inv_l = 1.0f / l_run;
-    if (a.max_spans == 1) {  // nothing to merge: the output row itself, half, P32
+    uint2 o[RT];
 #pragma unroll
-        for (int i = 0; i < RT; ++i) {
-            uint2 o = {packh2(o_acc[i][0] * inv_l, o_acc[i][1] * inv_l), packh2(o_acc[i][2] * inv_l, o_acc[i][3] * inv_l)};
-            *(uint2 *)(a.out + p32_offset(a.out_row0 + j, (kvh * G + col) * HD + 16 * i + 4 * g4, a.Hq * HD)) = o;
+    for (int i = 0; i < RT; ++i)
+        o[i] = uint2{packh2(o_acc[i][0] * inv_l, o_acc[i][1] * inv_l), packh2(o_acc[i][2] * inv_l, o_acc[i][3] * inv_l)};
+    if (!whole && pair == 0 && lane == 0) a.seq_parts[seq] = int2{w, n_pairs == np ? 1 : (at + np - 1) / per - w + 1};
+    if (col < G) {
+        if (n_pairs == np) {  // nothing to merge: the output row itself, P32
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+                *(uint2 *)(a.out + p32_offset(a.out_row0 + j, (kvh * G + col) * HD + 16 * i + 4 * g4, a.Hq * HD)) = o[i];
+        } else {
+            const size_t item = (size_t)(w + seq) * G + col;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) *(uint2 *)(a.part_o + item * HD + 16 * i + 4 * g4) = o[i];
+            if (g4 == 0) {
+                float2 ml = {m_run, l_run};
+                *(float2 *)(a.part_ml + item * 2) = ml;
+            }
         }
-        return;
     }
-    f16_t *po = a.part_o + (item * G + col) * HD;
-#pragma unroll
-    for (int i = 0; i < RT; ++i) {
-        uint2 o = {packh2(o_acc[i][0] * inv_l, o_acc[i][1] * inv_l), packh2(o_acc[i][2] * inv_l, o_acc[i][3] * inv_l)};
-        *(uint2 *)(po + 16 * i + 4 * g4) = o;
     }
-    if (g4 == 0) {
-        float2 ml = {m_run, l_run};
-        *(float2 *)(a.part_ml + (item * G + col) * 2) = ml;
+    todo -= n_pairs, at += n_pairs, pair = 0;
+    if (++kvh == a.Hkv) kvh = 0, ++j, len = todo > 0 ? __builtin_amdgcn_readfirstlane(decode_len(a, j)) : 0;
     }
 }
 
-// Merge of the span results of one (request, query head): with w_s = 2^(m_s - m) l_s and o_s the span's normalised
-// output, o = sum_s w_s o_s / sum_s w_s, spans taken in order.  One wavefront per (request, query head); output in P32 order for the O projection.
+// Merge of the partial results of one (request, query head): with w_s = 2^(m_s - m) l_s and o_s the normalised output of
+// its s-th stretch of keys, o = sum_s w_s o_s / sum_s w_s, in order.  One wavefront per (request, query head); output in
+// P32 order for the O projection.  A request that one wavefront swept whole has its output already.
 template <int HD, int G>
 __global__ __launch_bounds__(64) void attn_merge_kernel(AttnDecodeArgs a) {
     const int j = blockIdx.x / a.Hq, hq = blockIdx.x % a.Hq;
     const int kvh = hq / G, col = hq % G, lane = threadIdx.x;
-    const int len = a.ctx_len[j] + 1;
-    const int n_spans = (len + a.span - 1) / a.span;
-    const size_t item0 = ((size_t)j * a.Hkv + kvh) * a.max_spans;
+    const int2 parts = a.seq_parts[j * a.Hkv + kvh];
+    const int n_spans = min(parts.y, decode_pairs(decode_len(a, j)));
+    if (n_spans <= 1) return;
+    const size_t item0 = (size_t)parts.x + j * a.Hkv + kvh;
     constexpr int EPL = HD / 64;
     float acc[EPL], m = -INFINITY, denom = 0.f;
 #pragma unroll

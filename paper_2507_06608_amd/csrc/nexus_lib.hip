@@ -80,7 +80,8 @@ struct PhaseWs {
     bf16_t *xbuf[2] = {nullptr, nullptr};  // layer ping-pong, row-major [maxT][hidden]
     float *partial = nullptr;
     size_t partial_elems = 0;
-    float *part_o = nullptr, *part_ml = nullptr;  // decode attention split results
+    float *part_o = nullptr, *part_ml = nullptr;  // attention split results
+    int2 *seq_parts = nullptr;                    // decode attention: where a request's split results are
     int q_rows = 0;
 };
 
@@ -510,16 +511,15 @@ template <int HD>
 static int launch_attn_decode(const PhaseRun &r, const AttnDecodeArgs &a) {
     nexus_ctx *c = r.c;
     const int G = c->m.n_q_heads / c->m.n_kv_heads;
-    const int items = a.n_reqs * c->m.n_kv_heads * a.max_spans;
-    dim3 grid((items + kDecWaves - 1) / kDecWaves), mgrid(a.n_reqs * c->m.n_q_heads);
+    dim3 grid(decode_grid(a.n_reqs, c->m.n_kv_heads, a.max_ctx)), mgrid(a.n_reqs * c->m.n_q_heads);
 #define NX_DEC_CASE(GG)                                                                           \
     case GG: {                                                                                    \
         {                                                                                         \
             Tracer tr(c, r.phase, NEXUS_K_ATTN_DECODE, r.s);                                      \
-            hipLaunchKernelGGL((attn_decode_kernel<HD, GG>), grid, dim3(64 * kDecWaves), 0, r.s, a);         \
+            hipLaunchKernelGGL((attn_decode_kernel<HD, GG>), grid, dim3(64), 0, r.s, a);          \
         }                                                                                         \
         HIP_TRY(hipGetLastError());                                                               \
-        if (a.max_spans > 1) {                                                                    \
+        if (a.max_ctx > kDecWholeCtx) {                                                           \
             Tracer tr(c, r.phase, NEXUS_K_ATTN_MERGE, r.s);                                       \
             hipLaunchKernelGGL((attn_merge_kernel<HD, GG>), mgrid, dim3(64), 0, r.s, a);          \
         }                                                                                         \
@@ -596,18 +596,19 @@ static int run_layer(const PhaseRun &r, int layer, const bf16_t *x_in, bf16_t *y
             const int lead = r.pb->n_reqs - r.fused_decode;
             AttnDecodeArgs d{};
             d.q = ws.q, d.ctx_len = r.pb->prefix_len + lead, d.page_table = r.pb->page_table + (size_t)lead * r.pb->max_pages;
-            d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.span = plan_span(d.n_reqs, m.n_kv_heads, r.fused_max_ctx), d.max_spans = (r.fused_max_ctx + d.span - 1) / d.span;
+            d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.max_ctx = r.fused_max_ctx;
             d.k_pool = k_pool, d.v_pool = v_pool, d.n_pages = r.kv->n_pages, d.Hq = m.n_q_heads, d.Hkv = m.n_kv_heads;
             d.scale_log2e = scale_log2e, d.part_o = (f16_t *)c->ws[NEXUS_PHASE_DECODE].part_o, d.part_ml = c->ws[NEXUS_PHASE_DECODE].part_ml;
+            d.seq_parts = c->ws[NEXUS_PHASE_DECODE].seq_parts;
             d.out = ws.attn, d.lead_cu = r.pb->cu_chunk, d.n_lead = lead, d.out_row0 = r.pb->n_tokens - r.fused_decode;
             NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, d) : launch_attn_decode<64>(r, d));
         }
     } else {
         AttnDecodeArgs a{};
         a.q = ws.q, a.ctx_len = r.db->ctx_len, a.page_table = r.db->page_table, a.n_reqs = r.db->n_reqs;
-        a.max_pages = r.db->max_pages, a.span = plan_span(a.n_reqs, m.n_kv_heads, r.db->max_ctx), a.max_spans = (r.db->max_ctx + a.span - 1) / a.span;
+        a.max_pages = r.db->max_pages, a.max_ctx = r.db->max_ctx;
         a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
-        a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.out = ws.attn;
+        a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.seq_parts = ws.seq_parts, a.out = ws.attn;
         NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, a) : launch_attn_decode<64>(r, a));
     }
     // x1 = x + attn W_o^T, h2 = RMSNorm(x1): when the projection is split along K its reduction, the residual add
@@ -815,7 +816,7 @@ void nexus_destroy(nexus_ctx *c) {
     }
     for (auto &w : c->ws) {
         (void)hipFree(w.h), (void)hipFree(w.qkv), (void)hipFree(w.q), (void)hipFree(w.attn), (void)hipFree(w.x1), (void)hipFree(w.act);
-        (void)hipFree(w.xbuf[0]), (void)hipFree(w.xbuf[1]), (void)hipFree(w.partial), (void)hipFree(w.part_o), (void)hipFree(w.part_ml);
+        (void)hipFree(w.xbuf[0]), (void)hipFree(w.xbuf[1]), (void)hipFree(w.partial), (void)hipFree(w.part_o), (void)hipFree(w.part_ml), (void)hipFree(w.seq_parts);
     }
     (void)hipFree(c->rope_tab);
     (void)hipFree(c->probe_counts);
@@ -847,7 +848,8 @@ static int alloc_phase_ws(nexus_ctx *c, int phase, int maxT, int max_reqs) {
         NX_TRY(dev_alloc(&w.part_ml, items * 2, false));
     } else {
         NX_TRY(dev_alloc(&w.q, (size_t)maxT * c->q_dim, true));
-        const size_t items = max_span_items(maxT, m.n_kv_heads, c->lim.max_positions) * (m.n_q_heads / m.n_kv_heads);
+        const size_t items = decode_part_slots(maxT, m.n_kv_heads) * (m.n_q_heads / m.n_kv_heads);
+        NX_TRY(dev_alloc(&w.seq_parts, (size_t)maxT * m.n_kv_heads, true));
         NX_TRY(dev_alloc(&w.part_o, (items * m.head_dim + 1) / 2, false));  // half elements
         NX_TRY(dev_alloc(&w.part_ml, items * 2, false));
     }
@@ -1191,8 +1193,8 @@ static size_t carve_decode_ws(const nexus_ctx *c, int T, int max_ctx, bool multi
         ws.xbuf[1] = (bf16_t *)take((size_t)T * m.hidden * 2);
     }
     *zero_bytes = off;
-    const int span = plan_span(T, m.n_kv_heads, max_ctx);
-    const size_t items = (size_t)T * m.n_q_heads * ((max_ctx + span - 1) / span);  // (request, kv head, span) x the G heads of the kv head
+    const size_t items = max_ctx > kDecWholeCtx ? decode_part_slots(T, m.n_kv_heads) * (m.n_q_heads / m.n_kv_heads) : 0;
+    ws.seq_parts = (int2 *)take((size_t)T * m.n_kv_heads * sizeof(int2));
     ws.part_o = (float *)take(items * m.head_dim * 2);  // half elements
     ws.part_ml = (float *)take(items * 2 * 4);
     size_t pe = 0;

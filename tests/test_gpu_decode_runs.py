@@ -1,6 +1,7 @@
-"""Decode attention at every span length the batch size selects (64 .. 1024 keys per work item, and the single span whose
-output is not merged), with contexts on both sides of the span boundaries: sampled requests of each batch against the
-oracle, at the parity bar of the other cases."""
+"""Decode attention cut into runs of equal length over requests and kv heads: run lengths from the shortest to several
+requests per run, requests cut into many runs, more requests than one scan places, and the batch whose outputs are not
+merged, with contexts on both sides of the 32-key pairs and of the 1024 keys whose page ids are read at once: sampled
+requests of each batch against the oracle, at the parity bar of the other cases."""
 import numpy as np
 import pytest
 import torch
@@ -28,17 +29,18 @@ def oracle():
 
 # (requests, contexts that are always there, largest other context): 8 kv heads each
 CASES = [
-    ("one span of 256, no merge", 5, [0, 15, 16, 254, 255], 255),
-    ("spans of 64", 3, [63, 64, 65], 700),
-    ("spans of 128", 16, [127, 128, 129, 255, 256, 257], 1000),
-    ("spans of 256", 40, [255, 256, 257, 511, 512], 1500),
-    ("spans of 512", 300, [511, 512, 513, 1023, 1024, 1025, 2047, 2048], 2060),
-    ("spans of 1024", 600, [1022, 1023, 1024, 1025, 0], 1100),
+    ("whole contexts, no merge", 5, [0, 15, 16, 254, 255], 255),
+    ("shortest runs", 3, [63, 64, 65], 700),
+    ("one long request", 1, [8191], 8191),
+    ("runs of two pairs", 16, [31, 32, 33, 127, 128, 129], 1000),
+    ("runs longer than a window of page ids", 24, [1022, 1023, 1024, 1055, 1056, 8190], 8191),
+    ("several requests a run", 300, [0, 31, 32, 1023, 1024, 2047, 2048], 2060),
+    ("more requests than one scan", 600, [1022, 1023, 1024, 1025, 0], 1100),
 ]
 
 
 @pytest.mark.parametrize("name,n,edges,top", CASES, ids=[c[0] for c in CASES])
-def test_every_span_length(nx, oracle, name, n, edges, top):
+def test_equal_runs(nx, oracle, name, n, edges, top):
     print(f"[case] decode attention, {name}", flush=True)
     sh = synth.SHAPES["tiny"]
     rng = np.random.default_rng(n)
@@ -52,7 +54,7 @@ def test_every_span_length(nx, oracle, name, n, edges, top):
     torch.cuda.synchronize()
     ctx.decode_step(db, kv)
     ctx.sync()
-    sampled = list(range(len(edges))) + [n - 1] if n > len(edges) else list(range(n))
+    sampled = sorted(set(range(len(edges))) | {n // 2, n - 1})
     sub = synth.subset_for_oracle(wl, [], sampled)
     ref = run_oracle(oracle, sub, w)
     assert_close(name, f32(db.y[sampled]), ref["y_d"])
