@@ -105,8 +105,7 @@ struct nexus_ctx {
     nexus_model_desc m{};
     nexus_limits lim{};
     int device = 0, n_cus = 0, n_xcd = 8, cus_per_xcd = 32;
-    bool allow_p256 = true;
-    int force_tile = 0;  // test hook: 256 = 256 x 256 tiles wherever the shape allows, 384 = 256 x 128, 320 = 320 x 256, 128
+    const struct TileShape *force_tile = nullptr;  // test hook: the tile shape of every projection of more than 128 tokens
     int q_dim = 0, kv_dim = 0, n_qkv = 0;
     std::vector<LayerW> layers;
     PhaseWs ws[2];
@@ -169,17 +168,19 @@ static int dev_alloc(T **p, size_t elems, bool zero) {
 }
 
 // ---------------------------------------------------------------------------------------------- GEMM planning
-// Tile shapes (features x tokens), wavefronts, k per stage, ring depth.  Measured on MI355X: 128x128 tiles with
-// several workgroups per CU beat 256x256 at the token counts of a prefill chunk (and quantise far better on a CU
-// share); a batch of at most 128 tokens (a decode batch, a short chunk) streams the weights once and wants many
-// small workgroups whose rings together keep about 100 KiB per CU in flight: one CU draws at most about 50 GB/s
-// from HBM, so a decode share of the chip is bound by per-CU bytes in flight, not by the HBM interface.
+// Tile shapes are features x tokens.  A batch of at most 128 tokens (a decode batch, a short chunk) streams the weights
+// once and wants many small workgroups whose rings together keep about 100 KiB per CU in flight: one CU draws at
+// most about 50 GB/s from HBM, so a decode share of the chip is bound by per-CU bytes in flight, not by the HBM
+// interface.  Longer batches take the tiled kernel in one of the shapes of kTileShapes.
 enum GemmVariant {
-    GV_P128 = 0,  // gemm_dl_kernel, 128 x 128, 4 waves, 32-wide stages, 64 KiB ring: two workgroups per CU
-    GV_P256,      // gemm_dl_kernel, 256 x 256, 8 waves, 128 KiB ring: half the LDS and L2 traffic per flop, for GEMMs
-                  //   with several such tiles per CU of the share (same per-element summation order as GV_P128)
-    GV_P256x128,  // gemm_dl_kernel, 256 features x 128 tokens, 4 waves of 4 x 2 MFMA tiles, 96 KiB ring, one workgroup per
-                  //   CU: between the two in traffic per flop, for grids that the 256 x 256 tiles quantise badly
+    GV_P128 = 0,   // gemm_dl_kernel, 128 x 128, 4 waves, 32-wide stages, 64 KiB ring: two workgroups per CU
+    GV_P128D,      // the same with a six-stage ring, 96 KiB: one workgroup per CU
+    GV_P192x128,   // 4 waves of 3 x 2 MFMA tiles, 120 KiB ring (all from here on: one workgroup per CU)
+    GV_P256x128,   // 4 waves of 4 x 2, 144 KiB
+    GV_P320x128,   // 4 waves of 5 x 2, 140 KiB
+    GV_P192x256,   // 8 waves of 3 x 2, 140 KiB
+    GV_P256,       // 256 x 256, 8 waves of 2 x 4, 128 KiB
+    GV_P320,       // 320 x 256, 8 waves of 5 x 2, 144 KiB
     GV_S64,       // gemm_stream_kernel, 128 features x 64 tokens, 4 waves: decode batches of 33..64
     GV_S32,       // gemm_stream_kernel, 128 features x 32 tokens, 4 waves: decode batches of at most 32
     GV_S64W,      // gemm_stream_kernel, 256 features x 64 tokens (two feature strips per wave): on a small CU share
@@ -190,9 +191,6 @@ enum GemmVariant {
     GV_S128W,     // gemm_stream_kernel, 256 features x 128 tokens, 8 waves sharing the activation tiles
     GV_R64,       // gemm_dl_kernel with the extent of GV_S64 / GV_S32: k ranges shorter than the streaming
     GV_R32,       //   kernel's pipeline (hidden sizes below 128)
-    GV_P320,      // gemm_dl_kernel, 320 features x 256 tokens, 8 waves of 5 x 2 MFMA tiles, 144 KiB ring: for a QKV
-                  //   projection whose width is a multiple of 320 (10240 of the 70B-shaped layer: 256 tiles for a
-                  //   2048-token chunk, one round of the whole chip where 256 x 256 tiles need a round and a quarter)
     GV_COUNT
 };
 struct GemmPlan {
@@ -200,35 +198,101 @@ struct GemmPlan {
 };
 constexpr int kChipCUs = 256;  // the plan is sized for the whole chip, whatever share the phase runs on
 
+// The tiled GEMM's time, from which tile shape and split count are chosen.  A CU fills its LDS at 65 GB/s at most, and at
+// 40 GB/s the whole chip is at its power limit (1.35 PFLOP/s), so the time of a tile per 64 steps of k depends on the
+// shape and on how many CUs are busy: `us` holds it for 64, 128, 192 and 256 of them, measured on MI355X as the slope
+// between K = 1024, 4096 and 8192 of grids that fill those CUs once and twice.  `round_us` is what a round of the grid
+// pays on top (pipeline fill, epilogue).  Two 128 x 128 workgroups share a CU: `us` is the time of such a pair, and a lone
+// one takes kLoneTileUs.  Against 340 timings (256 to 1021 tokens, 1 to 4 slices, 192 and 256 CUs) the estimate is off by
+// 7 % in the mean.
+struct TileShape {
+    int variant, FS, TS, per_cu;
+    double us[4], round_us;
+    const char *name;  // test hook: NEXUS_GEMM_TILES
+};
+static const TileShape kTileShapes[] = {
+    {GV_P320, 10, 8, 1, {1.22, 1.31, 1.60, 1.90}, 11, "320"},     {GV_P256, 8, 8, 1, {1.08, 1.18, 1.30, 1.58}, 8, "256"},
+    {GV_P192x256, 6, 8, 1, {0.95, 1.06, 1.14, 1.25}, 7, "192x256"}, {GV_P320x128, 10, 4, 1, {0.90, 0.97, 1.04, 1.15}, 4, "320x128"},
+    {GV_P256x128, 8, 4, 1, {0.76, 0.82, 0.87, 0.93}, 4, "256x128"}, {GV_P192x128, 6, 4, 1, {0.60, 0.65, 0.69, 0.74}, 3, "192x128"},
+    {GV_P128D, 4, 4, 1, {0.48, 0.50, 0.52, 0.57}, 3, "128d"},     {GV_P128, 4, 4, 2, {0.93, 0.98, 1.05, 1.15}, 3, "128"},
+};
+constexpr double kLoneTileUs = 0.73;
+constexpr int kMaxTileSlices = 4;
+
+static double tile_round_us(const TileShape &t, int n) {  // one k step of 64 with n CUs busy
+    const double x = std::max(0.0, std::min(3.0, n / 64.0 - 1.0));
+    const int i = std::min(2, (int)x);
+    return t.us[i] + (t.us[i + 1] - t.us[i]) * (x - i);
+}
+static double tile_estimate_us(const TileShape &t, int n_ttiles, int n_ftiles, int ksteps_per_split, int S, int cus) {
+    const long tiles = (long)((n_ttiles + t.TS - 1) / t.TS) * ((n_ftiles + t.FS - 1) / t.FS) * S, slots = (long)t.per_cu * cus;
+    const long full = tiles / slots, rem = tiles % slots;
+    const double round = tile_round_us(t, cus);
+    double last = 0.0;
+    if (rem && t.per_cu == 1) last = tile_round_us(t, (int)rem);
+    else if (rem) last = rem <= cus ? kLoneTileUs : kLoneTileUs + (round - kLoneTileUs) * (double)(rem - cus) / cus;
+    return 4.0 + (full * round + last) * ksteps_per_split + t.round_us * (double)(full + (rem > 0));
+}
+static bool fits_32bit_offsets(int n_strips, int Kp) { return (size_t)n_strips * Kp * 64 < ((size_t)1 << 32); }
+// The fastest shape for a GEMM in S slices on `cus` CUs; ties go to the larger tile.  (The two widest shapes address their
+// operands with 32-bit offsets; 256 x 256 has a second form that does not.)
+static const TileShape *choose_tile(int n_ttiles, int n_ftiles, int Kp, int ksteps_per_split, int S, int cus, double *us = nullptr) {
+    const TileShape *best = nullptr;
+    double best_us = 0.0;
+    for (const TileShape &t : kTileShapes) {
+        if ((t.variant == GV_P320 || t.variant == GV_P192x256) && !(fits_32bit_offsets(n_ftiles, Kp) && fits_32bit_offsets(n_ttiles, Kp))) continue;
+        const double e = tile_estimate_us(t, n_ttiles, n_ftiles, ksteps_per_split, S, cus);
+        if (!best || e < best_us) best = &t, best_us = e;
+    }
+    if (us) *us = best_us;
+    return best;
+}
+
 // Depends on the problem only (never on the CU share): S fixes the summation order, so results are bit-identical
 // across layouts.  Decode GEMMs are cut along K until there are about 200 workgroups (800 wavefronts, each
 // with its own weight stream in flight); measured on MI355X, more slices cost more in partial-sum traffic than
-// they gain.
-static GemmPlan plan_gemm(int T, int n_ftiles, int Kp) {
+// they gain.  Beyond 128 tokens S is the one with the least estimated time of GEMM and partial sums: these cost 0.29 us
+// per MB to write and to read back (the kernel that sums them reads S slices of fp32 where it would have read one of
+// half), and a reduce kernel of its own where no later kernel sums them in passing.
+static GemmPlan plan_gemm(int T, int n_ftiles, int Kp, bool own_reduce) {
     const int ksteps = Kp / kGemmBK;
     const int nt = (T + 31) / 32;
     GemmPlan p{};
-    int min_ksteps;
-    if (T <= 32) {
-        p.variant = GV_S32, p.FS = 4, p.TS = 1, min_ksteps = 8;
-    } else if (T <= 64) {
-        p.variant = GV_S64, p.FS = 4, p.TS = 2, min_ksteps = 8;
-    } else if (T <= 128) {
-        p.variant = GV_S128, p.FS = 4, p.TS = 4, min_ksteps = 8;
-    } else {
-        p.variant = GV_P128, p.FS = 4, p.TS = 4, min_ksteps = 16;
-    }
-    const int blocks = ((n_ftiles + p.FS - 1) / p.FS) * ((nt + p.TS - 1) / p.TS);
     int S = 1;
-    if (p.variant != GV_P128) {
+    if (T <= 128) {
+        const int min_ksteps = 8;
+        p.FS = 4;
+        if (T <= 32) p.variant = GV_S32, p.TS = 1;
+        else if (T <= 64) p.variant = GV_S64, p.TS = 2;
+        else p.variant = GV_S128, p.TS = 4;
+        const int blocks = ((n_ftiles + p.FS - 1) / p.FS) * ((nt + p.TS - 1) / p.TS);
         while (S < 8 && blocks * S < (3 * kChipCUs) / 4) S *= 2;
-    } else if (blocks < (3 * kChipCUs) / 4) {
-        S = std::min(4, (kChipCUs + blocks / 2) / blocks);
+        while (S > 1 && ksteps / S < min_ksteps) --S;
+    } else {
+        double best = 0.0;
+        for (int s = 1; s <= kMaxTileSlices && ksteps / s >= 8; ++s) {
+            double us;
+            choose_tile(nt, n_ftiles, Kp, (ksteps + s - 1) / s, s, kChipCUs, &us);
+            if (s > 1) us += (4 * s - 2) * 32.0 * nt * 32.0 * n_ftiles * 0.29e-6 + (own_reduce ? 5.0 : 0.0);
+            if (s == 1 || us < best) best = us, S = s;
+        }
     }
-    while (S > 1 && ksteps / S < min_ksteps) --S;
     p.ksteps_per_split = (ksteps + S - 1) / S;
     p.S = (ksteps + p.ksteps_per_split - 1) / p.ksteps_per_split;
+    if (T > 128) {
+        const TileShape *t = choose_tile(nt, n_ftiles, Kp, p.ksteps_per_split, p.S, kChipCUs);
+        p.variant = t->variant, p.FS = t->FS, p.TS = t->TS;
+    }
     return p;
+}
+// Elements of split-K partial sums of a batch of T tokens (the largest of the four projections).
+static size_t partial_need(int T, const int (&shapes)[4][2]) {
+    size_t pe = 0;
+    for (int i = 0; i < 4; ++i) {
+        const GemmPlan p = plan_gemm(T, shapes[i][0] / 32, p32_kp(shapes[i][1]), i == 2);
+        if (p.S > 1) pe = std::max(pe, (size_t)p.S * T * shapes[i][0]);
+    }
+    return pe;
 }
 
 template <int FS, int TS, int WF, int WT, int BKT, int NST, int EPI, bool ASM_READS = true, int NWL = 0, bool BUF_LOADS = false>
@@ -265,14 +329,16 @@ template <int EPI>
 static hipError_t launch_gemm_v(int variant, const GemmArgs &a, dim3 grid, hipStream_t s) {
     switch (variant) {
         case GV_P128: return launch_gemm_t<4, 4, 2, 2, 2, 4, EPI>(a, grid, s);
+        case GV_P128D: return launch_gemm_t<4, 4, 2, 2, 2, 6, EPI>(a, grid, s);
+        case GV_P192x128: return launch_gemm_t<6, 4, 2, 2, 2, 6, EPI>(a, grid, s);
+        case GV_P256x128: return launch_gemm_t<8, 4, 2, 2, 2, 6, EPI>(a, grid, s);
+        case GV_P320x128: return launch_gemm_t<10, 4, 2, 2, 2, 5, EPI>(a, grid, s);
+        case GV_P192x256: return launch_gemm_t<6, 8, 2, 4, 2, 5, EPI, true, 4, true>(a, grid, s);
         case GV_P256:  // buffer loads address an operand matrix with 32-bit offsets
-            if ((size_t)a.n_ftiles * a.Kp * 64 < ((size_t)1 << 32) && (size_t)a.n_ttiles * a.Kp * 64 < ((size_t)1 << 32))
+            if (fits_32bit_offsets(a.n_ftiles, a.Kp) && fits_32bit_offsets(a.n_ttiles, a.Kp))
                 return launch_gemm_t<8, 8, 4, 2, 2, 4, EPI, true, 4, true>(a, grid, s);
             return launch_gemm_t<8, 8, 4, 2, 2, 4, EPI, true, 4, false>(a, grid, s);
-        case GV_P256x128: return launch_gemm_t<8, 4, 2, 2, 2, 4, EPI>(a, grid, s);
-        case GV_P320:  // planned for the row-major epilogue and operands below 4 GiB only
-            if constexpr (EPI == EPI_ROWMAJOR) return launch_gemm_t<10, 8, 2, 4, 2, 4, EPI, true, 4, true>(a, grid, s);
-            return hipErrorInvalidValue;
+        case GV_P320: return launch_gemm_t<10, 8, 2, 4, 2, 4, EPI, true, 4, true>(a, grid, s);
         case GV_S64: return launch_gemm_stream_t<1, 2, 4, 4, kStreamDepth, EPI>(a, grid, s);
         case GV_S32: return launch_gemm_stream_t<1, 1, 4, 4, kStreamDepth, EPI>(a, grid, s);
         case GV_S64W: return launch_gemm_stream_t<2, 2, 4, 4, kStreamDepth, EPI>(a, grid, s);
@@ -336,7 +402,7 @@ static int run_gemm(const PhaseRun &r, int kernel_id, const f16_t *W, int N_pack
     PhaseWs &ws = *r.ws;
     const int Kp = p32_kp(K);
     const int n_ftiles = N_packed / 32;
-    const GemmPlan p = plan_gemm(r.T, n_ftiles, Kp);
+    const GemmPlan p = plan_gemm(r.T, n_ftiles, Kp, epi == EPI_SWIGLU);
     GemmArgs a{};
     a.W = W, a.X = X, a.n_ftiles = n_ftiles, a.n_ttiles = (r.T + 31) / 32, a.Kp = Kp;
     a.ksteps_per_split = p.ksteps_per_split;
@@ -345,38 +411,13 @@ static int run_gemm(const PhaseRun &r, int kernel_id, const f16_t *W, int N_pack
     a.out_p32 = out_p32, a.out_Kp = out_p32 ? p32_kp(out_K) : 0;
     a.partial = ws.partial;
     // Ring geometry and tile extent may follow the CU share (they do not change any element's summation order; the
-    // split factor S, which does, is problem-only).  Larger tiles move fewer operand bytes through LDS per flop but
-    // quantise worse on a given number of CUs.  The choice minimises the sum over the rounds of the grid of the time
-    // of one round, which depends on how many CUs the round keeps busy: the chip is power-limited under dense MFMA
-    // work and clocks higher when fewer CUs run it.  Fits to measurements on MI355X (the four projections of the 8B-
-    // and 70B-shaped layers on 128 ... 256 CUs), microseconds per 4096 elements of K, n = busy CUs: 256 x 256 tiles,
-    // one per CU, 72 + 0.14 max(0, n - 128) + 0.21 max(0, n - 192) plus 30 per launch for the fill and the drain of
-    // its last round; 256 x 128 tiles, one per CU, 55.5 + 0.06 max(0, n - 128); 128 x 128 tiles, two per CU,
-    // 60 + 0.0625 max(0, n - 128), 47 for a last round with at most one tile per CU.  Ties go to the larger tile.
+    // split factor S, which does, is problem-only).
     int variant = p.variant, FS = p.FS, TS = p.TS;
-    if (variant == GV_P128 && p.S == 1 && c->allow_p256) {
-        const long n128 = (long)((a.n_ttiles + 3) / 4) * ((n_ftiles + 3) / 4);
-        const long n256 = (long)((a.n_ttiles + 7) / 8) * ((n_ftiles + 7) / 8);
-        const long n256x128 = (long)((a.n_ttiles + 3) / 4) * ((n_ftiles + 7) / 8);
-        const double kscale = Kp / 4096.0;
-        auto total = [&](long tiles, int per_cu, auto round_us) {
-            const long slots = (long)per_cu * r.cus, rem = tiles % slots;
-            return kscale * ((double)(tiles / slots) * round_us(r.cus) + (rem ? round_us((int)((rem + per_cu - 1) / per_cu)) : 0.0));
-        };
-        const double est256 = 30.0 + total(n256, 1, [](int n) { return 72.0 + 0.14 * std::max(0, n - 128) + 0.21 * std::max(0, n - 192); });
-        const double est256x128 = total(n256x128, 1, [](int n) { return 55.5 + 0.06 * std::max(0, n - 128); });
-        double est128 = total(n128, 2, [](int n) { return 60.0 + 0.0625 * std::max(0, n - 128); });
-        if (n128 % (2L * r.cus) && n128 % (2L * r.cus) <= r.cus) est128 -= kscale * 13.0;  // last round: one tile per CU, 47
-        // 320 x 256 tiles: the 256 x 256 kernel with five instead of four MFMA tiles per wavefront along the features
-        // (1.25x the time per round), where the width divides and the epilogue is the plain one
-        double est320 = 1e30;
-        if (epi == EPI_ROWMAJOR && n_ftiles % 10 == 0 && (size_t)n_ftiles * Kp * 64 < ((size_t)1 << 32) && (size_t)a.n_ttiles * Kp * 64 < ((size_t)1 << 32))
-            est320 = 30.0 + 1.25 * total((long)((a.n_ttiles + 7) / 8) * (n_ftiles / 10), 1,
-                                         [](int n) { return 72.0 + 0.14 * std::max(0, n - 128) + 0.21 * std::max(0, n - 192); });
-        const double best = std::min(std::min(est256, est256x128), std::min(est128, est320));
-        if (c->force_tile ? (c->force_tile == 320 && est320 < 1e30) : est320 == best && est320 < est256) variant = GV_P320, FS = 10, TS = 8;
-        else if (c->force_tile ? c->force_tile == 256 : (est256 <= est128 && est256 <= est256x128)) variant = GV_P256, FS = 8, TS = 8;
-        else if (c->force_tile ? c->force_tile == 384 : est256x128 <= est128) variant = GV_P256x128, FS = 8, TS = 4;
+    if (r.T > 128) {
+        const TileShape *t = c->force_tile;
+        if (!t || ((t->variant == GV_P320 || t->variant == GV_P192x256) && !(fits_32bit_offsets(n_ftiles, Kp) && fits_32bit_offsets(a.n_ttiles, Kp))))
+            t = choose_tile(a.n_ttiles, n_ftiles, Kp, p.ksteps_per_split, p.S, r.cus);
+        variant = t->variant, FS = t->FS, TS = t->TS;
     }
     // Measured on 64 of the 256 CUs (T = 64): gate/up 113 -> 98 us, down 55 -> 48, O 21.6 -> 18.9 with the wide
     // variant, QKV (too few workgroups left) 27 -> 30; on 96 CUs and more the narrow one wins or ties.
@@ -862,11 +903,8 @@ static int alloc_phase_ws(nexus_ctx *c, int phase, int maxT, int max_reqs) {
     }
     size_t pe = 0;
     const int shapes[4][2] = {{c->n_qkv, m.hidden}, {m.hidden, c->q_dim}, {2 * m.ffn, m.hidden}, {m.hidden, m.ffn}};
-    for (auto &s : shapes)  // the split count depends on T, so take the worst case over every T the phase may see
-        for (int T = 1; T <= maxT; ++T) {
-            const GemmPlan p = plan_gemm(T, s[0] / 32, p32_kp(s[1]));
-            if (p.S > 1) pe = std::max(pe, (size_t)p.S * T * s[0]);
-        }
+    // the split count depends on T by strips of 32 tokens, so the worst case is at the end of some strip
+    for (int T = 32; T < maxT + 32; T += 32) pe = std::max(pe, partial_need(std::min(T, maxT), shapes));
     w.partial_elems = pe;
     NX_TRY(dev_alloc(&w.partial, pe, false));
     return NEXUS_OK;
@@ -907,12 +945,11 @@ int nexus_create(const nexus_model_desc *desc, const nexus_limits *limits, int d
         c->cus_per_xcd = c->n_cus / c->n_xcd;
         const char *order = getenv("NEXUS_CU_BIT_ORDER");
         c->bits_xcd_major = order && !strcmp(order, "xcd_major");
-        // test hook: one GEMM tile shape for every prefill projection ("128", "256", "256x128"; "320" where it applies), to compare the shapes
-        // bit for bit and to time them against each other
-        const char *tiles = getenv("NEXUS_GEMM_TILES");
-        c->allow_p256 = !(tiles && !strcmp(tiles, "128"));
-        c->force_tile = tiles && !strcmp(tiles, "256") ? 256 : tiles && !strcmp(tiles, "256x128") ? 384 : tiles && !strcmp(tiles, "128") ? 128
-                        : tiles && !strcmp(tiles, "320") ? 320 : 0;
+        // test hook: one GEMM tile shape (a name of kTileShapes) for every projection of more than 128 tokens, to compare
+        // the shapes bit for bit and to time them against each other
+        if (const char *tiles = getenv("NEXUS_GEMM_TILES"))
+            for (const TileShape &t : kTileShapes)
+                if (!strcmp(tiles, t.name)) c->force_tile = &t;
         if (const char *dbg = getenv("NEXUS_DEBUG_CHECKS")) c->debug_checks = atoi(dbg) != 0;
         if (const char *ml = getenv("NEXUS_MAX_LAYOUTS")) c->max_layouts = std::max(1, std::min(64, atoi(ml)));
         if (hipStreamCreateWithFlags(&c->s_main, hipStreamNonBlocking) != hipSuccess) { rc = fail(NEXUS_EHIP, "stream creation failed"); break; }
@@ -1197,12 +1234,8 @@ static size_t carve_decode_ws(const nexus_ctx *c, int T, int max_ctx, bool multi
     ws.seq_parts = (int2 *)take((size_t)T * m.n_kv_heads * sizeof(int2));
     ws.part_o = (float *)take(items * m.head_dim * 2);  // half elements
     ws.part_ml = (float *)take(items * 2 * 4);
-    size_t pe = 0;
     const int shapes[4][2] = {{c->n_qkv, m.hidden}, {m.hidden, c->q_dim}, {2 * m.ffn, m.hidden}, {m.hidden, m.ffn}};
-    for (auto &sh : shapes) {
-        const GemmPlan p = plan_gemm(T, sh[0] / 32, p32_kp(sh[1]));
-        if (p.S > 1) pe = std::max(pe, (size_t)p.S * T * sh[0]);
-    }
+    const size_t pe = partial_need(T, shapes);
     ws.partial_elems = pe;
     ws.partial = (float *)take(pe * 4);
     if (w) *w = ws;

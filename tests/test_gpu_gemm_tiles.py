@@ -1,0 +1,60 @@
+"""Every tile shape of the tiled GEMM against every other, bit for bit: per element they add the same products in the same
+order, so any shape must reproduce a chunk's outputs exactly, with ragged token counts (partial token tiles), widths that
+are no multiple of the tile (partial feature tiles), one to four K slices and K ranges shorter than the widest ring.  One
+of the runs is checked against the oracle at the parity bar of the other cases."""
+import pytest
+import torch
+
+from paper_2507_06608_amd import synth
+
+from tests.parity_util import assert_close, f32, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+TILES = ["128", "128d", "192x128", "256x128", "320x128", "192x256", "256", "320"]
+
+
+@pytest.fixture(scope="module")
+def nx():
+    from paper_2507_06608_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.fixture(scope="module")
+def oracle():
+    import oracle
+    oracle.lib()
+    return oracle
+
+
+@pytest.mark.parametrize("shape,chunks", [("tiny", [129]), ("tiny", [200, 133]), ("llama3_8b", [131]), ("qwen25_14b", [300, 77]), ("llama3_8b", [1033])],
+                         ids=["tiny 129", "tiny 333", "8B 131", "14B 377", "8B 1033"])
+def test_all_tile_shapes_agree(nx, oracle, monkeypatch, shape, chunks):
+    sh = synth.SHAPES[shape]
+    wl = synth.make_workload("tiles", sh, 3, chunk_lens=chunks, prefix_lens=[17] * len(chunks), decode_ctx=[], kv_device="cuda:0")
+    w = synth.make_weights(sh, 3)
+
+    def run(tiles):
+        print(f"[case] {shape} {chunks} tiles {tiles}", flush=True)
+        if tiles:
+            monkeypatch.setenv("NEXUS_GEMM_TILES", tiles)
+        else:
+            monkeypatch.delenv("NEXUS_GEMM_TILES", raising=False)
+        ctx = nx.context_for(wl)
+        ctx.load_layer(0, w)
+        kv = ctx.make_kv(wl.k_pool, wl.v_pool)
+        pb = nx.DevPrefill(wl.prefill, ctx.device)
+        torch.cuda.synchronize()
+        ctx.prefill_chunk(pb, kv)
+        ctx.sync()
+        y = pb.y.clone()
+        ctx.close()
+        return y
+
+    y = run(None)
+    if shape == "tiny":
+        ref = run_oracle(oracle, wl, w)
+        assert_close(f"{shape} {chunks}", f32(y), ref["y_p"])
+    for tiles in TILES:
+        assert torch.equal(run(tiles).view(torch.int16), y.view(torch.int16)), tiles
