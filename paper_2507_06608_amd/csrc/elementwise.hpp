@@ -334,8 +334,15 @@ __global__ __launch_bounds__(256) void rope_append_decode_kernel(RopeArgs a) {
 // the 8 lanes that share a line are neighbours.  Thread (j = tid % 8, tid / 8): token j of the group, one of 32
 // units in flight; a unit is a chunk of 8 rotary pairs of a head (q heads first, then k heads) or 8 value elements.
 // The values of a unit pass through LDS to change hands: lane j then holds element j of the unit for the 8 tokens.
-// Grid: x = 4 groups per 32-row tile of the request-aligned query rows (at least the batch's tile count), y = the
-// workgroups that share a group's units (short batches have too few groups to fill the chip).
+// The units come in blocks of 32 of one kind.  Grid: x = 4 groups per 32-row tile of the request-aligned query rows (at
+// least the batch's tile count), y = the workgroups that share a group's blocks.  A short batch is bound by the chain of
+// loads in front of its stores: as many workgroups as there are blocks (14 of the 8B shape) walk one block each (45
+// tokens: 6.5 us, 11.3 with eight workgroups of up to three rounds each; 512 tokens and two K slices 10.7, 14.0).  A long batch is bound by the bytes in flight, hence the
+// form without split-K sums, which needs half the registers (8192 tokens: 61 us, 73.7 with the registers of both).
+__host__ __device__ __forceinline__ int rope_unit_blocks(const RopeArgs &a) {
+    return ((a.Hq + a.Hkv) * (a.hd >> 4) + 31) / 32 + (a.Hkv * (a.hd >> 3) + 31) / 32;
+}
+template <bool PARTIAL>  // the projection was split along K
 __global__ __launch_bounds__(256) void rope_append_prefill_kernel(RopeArgs a) {
     __shared__ uint4 vst[32][9];  // [unit in flight][token] (+ 1: the transposed reads spread over the banks)
     const int b = xcd_run_index(blockIdx.x, gridDim.x);
@@ -367,7 +374,7 @@ __global__ __launch_bounds__(256) void rope_append_prefill_kernel(RopeArgs a) {
     const int slot = pos & 15;
     const float2 *tab = a.rope_tab + (size_t)(pos < a.n_pos ? pos : a.n_pos - 1) * half;
     auto load8 = [&](int col, float (&o)[8]) {
-        if (a.partial) {
+        if constexpr (PARTIAL) {
             sum_slices8(a.partial + (size_t)t * width + col, (size_t)a.T * width, a.S, o);
             if (a.bias) {
                 const uint4 bb = *(const uint4 *)(a.bias + col);
@@ -385,15 +392,17 @@ __global__ __launch_bounds__(256) void rope_append_prefill_kernel(RopeArgs a) {
         }
     };
     const int rope_units = (a.Hq + a.Hkv) * cph;
-    const int uy = 32 * blockIdx.y, ustep = 32 * gridDim.y;  // the units are dealt to gridDim.y workgroups, 32 at a time
+    const int rope_blocks = (rope_units + 31) / 32, blocks = rope_unit_blocks(a);
     // cph divides 32 (head dimensions 64 and 128): a thread's units all have the same pair chunk, whose eight
     // (cos, sin) it reads once instead of once per head
     const int c = ul % cph;
     float2 cs[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) cs[e] = tab[c * 8 + e];
-    for (int u = uy + ul; u < rope_units; u += ustep) {
-        if (!tok_ok) continue;
+    int blk = blockIdx.y;  // the same for the whole workgroup, so are the trip counts of both loops
+    for (; blk < rope_blocks; blk += gridDim.y) {
+        const int u = 32 * blk + ul;
+        if (!tok_ok || u >= rope_units) continue;
         const int h = u / cph;
         float xl[8], xh[8], ol[8], oh[8];
         load8(h * hd + c * 8, xl);
@@ -419,9 +428,10 @@ __global__ __launch_bounds__(256) void rope_append_prefill_kernel(RopeArgs a) {
     // whole, aligned token group of one page; single elements otherwise (ragged tail, prefix not a multiple of 8)
     const int v_units = a.Hkv * (hd >> 3);
     const bool whole = (pos0 & 7) == 0 && local0 + 8 <= n_r;
-    const int page0 = whole ? page_of(pos0) : -1;
-    for (int ub = uy; ub < v_units; ub += ustep) {  // uniform trip count: the barriers below are the workgroup's
-        const int u = ub + ul;
+    // the group's tokens lie in one page or two: both looked up here, not one lookup per token between the stores
+    const int page0 = page_of(pos0), page1 = whole ? -1 : page_of(pos0 + 7);
+    for (; blk < blocks; blk += gridDim.y) {
+        const int u = 32 * (blk - rope_blocks) + ul;
         const bool unit_ok = u < v_units;
         const int kvh = unit_ok ? u / (hd >> 3) : 0, c = unit_ok ? u % (hd >> 3) : 0;
         float vv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -442,9 +452,8 @@ __global__ __launch_bounds__(256) void rope_append_prefill_kernel(RopeArgs a) {
             } else {
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
-                    if (local0 + k >= n_r) break;
-                    const int pk = page_of(pos0 + k);
-                    if (pk >= 0) (a.v_pool + ((size_t)pk * a.Hkv + kvh) * (kPage * hd))[vblk_offset((pos0 + k) & 15, c * 8 + j, hd)] = el[k];
+                    const int pk = (pos0 + k) >> 4 == pos0 >> 4 ? page0 : page1;
+                    if (pk >= 0 && local0 + k < n_r) (a.v_pool + ((size_t)pk * a.Hkv + kvh) * (kPage * hd))[vblk_offset((pos0 + k) & 15, c * 8 + j, hd)] = el[k];
                 }
             }
         }

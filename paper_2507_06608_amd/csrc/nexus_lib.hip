@@ -531,7 +531,8 @@ static int launch_attn_prefill(const PhaseRun &r, const AttnPrefillArgs &base) {
         HIP_TRY(hipGetLastError());                                                                                  \
         if (a.n_splits > 1) {                                                                                        \
             Tracer tr(c, r.phase, NEXUS_K_ATTN_MERGE, r.s);                                                          \
-            hipLaunchKernelGGL((attn_prefill_merge_kernel<HD, SPB>), dim3((r.T - r.fused_decode) * ((c->m.n_q_heads * HD + 511) / 512)), dim3(64), 0, r.s, a); /* decode rows of a fused batch are not this kernel's */ \
+            const int rows = r.T - r.fused_decode; /* decode rows of a fused batch are not this kernel's */              \
+            hipLaunchKernelGGL((attn_prefill_merge_kernel<HD, SPB>), dim3((rows + kMergeRows - 1) / kMergeRows, (c->m.n_q_heads * HD + kMergeCols - 1) / kMergeCols), dim3(256), 0, r.s, a, rows); \
         }                                                                                                            \
         break;                                                                                                       \
     }
@@ -613,10 +614,14 @@ static int run_layer(const PhaseRun &r, int layer, const bf16_t *x_in, bf16_t *y
         a.max_pages = prefill ? r.pb->max_pages : r.db->max_pages;
         a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.q_out = ws.q;
         Tracer tr(c, r.phase, NEXUS_K_ROPE_APPEND, r.s);
-        // prefill: 4 groups of 8 rows per 32-row tile of the request-aligned rows (at most T / 32 + n_reqs tiles)
-        const int groups = 4 * (r.T / 32 + a.n_reqs);
-        const int share = std::max(1, std::min(8, 2048 / groups));  // workgroups per group, so that ~2048 are in the grid
-        if (prefill) hipLaunchKernelGGL(rope_append_prefill_kernel, dim3(groups, share), dim3(256), 0, r.s, a);
+        if (prefill) {
+            // 4 groups of 8 rows per 32-row tile of the request-aligned rows (at most T / 32 + n_reqs tiles); the workgroups
+            // that share a group's blocks of 32 units: as many as there are blocks, while ~2048 are in the grid
+            const int groups = 4 * (r.T / 32 + a.n_reqs);
+            const int share = std::max(1, std::min(rope_unit_blocks(a), 2048 / groups));
+            if (a.partial) hipLaunchKernelGGL(rope_append_prefill_kernel<true>, dim3(groups, share), dim3(256), 0, r.s, a);
+            else hipLaunchKernelGGL(rope_append_prefill_kernel<false>, dim3(groups, share), dim3(256), 0, r.s, a);
+        }
         else hipLaunchKernelGGL(rope_append_decode_kernel, dim3(r.T, std::max(1, std::min(4, 256 / std::max(1, r.T)))), dim3(256), 0, r.s, a);
         HIP_TRY(hipGetLastError());
     }
