@@ -491,9 +491,7 @@ static int run_rmsnorm(const PhaseRun &r, const void *x, const bf16_t *g, f16_t 
         else if (d <= 4096) NX_RMS_WAVE(8)
         else NX_RMS_WAVE(16)
 #undef NX_RMS_WAVE
-    } else if (d <= 2048) hipLaunchKernelGGL((rmsnorm_kernel<1, IN>), dim3(r.T), dim3(256), 0, r.s, x, g, out_p32, d, Kp, c->m.rms_eps, pp);
-    else if (d <= 4096) hipLaunchKernelGGL((rmsnorm_kernel<2, IN>), dim3(r.T), dim3(256), 0, r.s, x, g, out_p32, d, Kp, c->m.rms_eps, pp);
-    else hipLaunchKernelGGL((rmsnorm_kernel<4, IN>), dim3(r.T), dim3(256), 0, r.s, x, g, out_p32, d, Kp, c->m.rms_eps, pp);
+    } else hipLaunchKernelGGL(rmsnorm_kernel<IN>, dim3(r.T), dim3(rmsnorm_threads(d)), 0, r.s, x, g, out_p32, d, Kp, c->m.rms_eps, pp);
     HIP_TRY(hipGetLastError());
     return NEXUS_OK;
 }
@@ -622,7 +620,7 @@ static int run_layer(const PhaseRun &r, int layer, const bf16_t *x_in, bf16_t *y
             if (a.partial) hipLaunchKernelGGL(rope_append_prefill_kernel<true>, dim3(groups, share), dim3(256), 0, r.s, a);
             else hipLaunchKernelGGL(rope_append_prefill_kernel<false>, dim3(groups, share), dim3(256), 0, r.s, a);
         }
-        else hipLaunchKernelGGL(rope_append_decode_kernel, dim3(r.T, std::max(1, std::min(4, 256 / std::max(1, r.T)))), dim3(256), 0, r.s, a);
+        else hipLaunchKernelGGL(rope_append_decode_kernel, dim3(r.T, ((a.Hq + a.Hkv) * (a.hd >> 4) + a.Hkv * (a.hd >> 3) + kRopeDecThreads - 1) / kRopeDecThreads), dim3(kRopeDecThreads), 0, r.s, a);
         HIP_TRY(hipGetLastError());
     }
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)m.head_dim);
