@@ -582,7 +582,14 @@ static int launch_attn_decode(const PhaseRun &r, const AttnDecodeArgs &a) {
 // residual in x1; x_in (that layer's output) is still unwritten and this layer's first norm produces it.
 // defer_down (may be null): when given and this layer's down projection is split along K, its slices are left for
 // the next layer in the same way and *defer_down receives their number, else 0.
-static int run_layer(const PhaseRun &r, int layer, const bf16_t *x_in, bf16_t *y_out, int down_pending, int *defer_down) {
+// A layer is enqueued in kLayerStages stages of one to three launches, in order; what one stage leaves for the next is
+// in `carry`.
+constexpr int kLayerStages = 5;
+struct LayerCarry {
+    int qkv_slices = 0, o_slices = 0;
+};
+static int run_layer_stage(const PhaseRun &r, int layer, int stage, LayerCarry &carry, const bf16_t *x_in, bf16_t *y_out, int down_pending,
+                           int *defer_down) {
     nexus_ctx *c = r.c;
     const nexus_model_desc &m = c->m;
     PhaseWs &ws = *r.ws;
@@ -591,95 +598,105 @@ static int run_layer(const PhaseRun &r, int layer, const bf16_t *x_in, bf16_t *y
     bf16_t *k_pool = (bf16_t *)((char *)r.kv->k_pool + (size_t)layer * r.kv->layer_stride_bytes);
     bf16_t *v_pool = (bf16_t *)((char *)r.kv->v_pool + (size_t)layer * r.kv->layer_stride_bytes);
 
-    if (down_pending) {
-        RmsPartial pp{ws.partial, down_pending, r.T, nullptr, nullptr, ws.x1, const_cast<bf16_t *>(x_in)};
-        NX_TRY(run_rmsnorm<RMS_IN_PARTIAL_Y>(r, nullptr, L.g1, ws.h, pp));
-    } else {
-        NX_TRY(run_rmsnorm<RMS_IN_BF16>(r, x_in, L.g1, ws.h));
+    if (stage == 0) {
+        if (down_pending) {
+            RmsPartial pp{ws.partial, down_pending, r.T, nullptr, nullptr, ws.x1, const_cast<bf16_t *>(x_in)};
+            NX_TRY(run_rmsnorm<RMS_IN_PARTIAL_Y>(r, nullptr, L.g1, ws.h, pp));
+        } else {
+            NX_TRY(run_rmsnorm<RMS_IN_BF16>(r, x_in, L.g1, ws.h));
+        }
+        // a split-K QKV projection is summed by the rotary kernel
+        return run_gemm(r, NEXUS_K_GEMM_QKV, L.wqkv, c->n_qkv, ws.h, m.hidden, EPI_ROWMAJOR, ws.qkv, nullptr, L.bqkv, c->n_qkv,
+                        nullptr, 0, &carry.qkv_slices);
     }
-    int qkv_slices = 0;  // a split-K QKV projection is summed by the rotary kernel
-    NX_TRY(run_gemm(r, NEXUS_K_GEMM_QKV, L.wqkv, c->n_qkv, ws.h, m.hidden, EPI_ROWMAJOR, ws.qkv, nullptr, L.bqkv, c->n_qkv,
-                    nullptr, 0, &qkv_slices));
-    {
-        RopeArgs a{};
-        a.partial = qkv_slices ? ws.partial : nullptr, a.S = qkv_slices, a.bias = L.bqkv;
-        a.qkv = ws.qkv, a.T = r.T, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads, a.hd = m.head_dim;
-        a.rope_tab = c->rope_tab, a.n_pos = c->lim.max_positions;
-        a.cu_chunk = prefill ? r.pb->cu_chunk : nullptr;
-        a.pos_base = prefill ? r.pb->prefix_len : r.db->ctx_len;
-        a.n_reqs = prefill ? r.pb->n_reqs : r.db->n_reqs;
-        a.page_table = prefill ? r.pb->page_table : r.db->page_table;
-        a.max_pages = prefill ? r.pb->max_pages : r.db->max_pages;
-        a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.q_out = ws.q;
-        Tracer tr(c, r.phase, NEXUS_K_ROPE_APPEND, r.s);
+    if (stage == 1) {
+        const int qkv_slices = carry.qkv_slices;
+        {
+            RopeArgs a{};
+            a.partial = qkv_slices ? ws.partial : nullptr, a.S = qkv_slices, a.bias = L.bqkv;
+            a.qkv = ws.qkv, a.T = r.T, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads, a.hd = m.head_dim;
+            a.rope_tab = c->rope_tab, a.n_pos = c->lim.max_positions;
+            a.cu_chunk = prefill ? r.pb->cu_chunk : nullptr;
+            a.pos_base = prefill ? r.pb->prefix_len : r.db->ctx_len;
+            a.n_reqs = prefill ? r.pb->n_reqs : r.db->n_reqs;
+            a.page_table = prefill ? r.pb->page_table : r.db->page_table;
+            a.max_pages = prefill ? r.pb->max_pages : r.db->max_pages;
+            a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.q_out = ws.q;
+            Tracer tr(c, r.phase, NEXUS_K_ROPE_APPEND, r.s);
+            if (prefill) {
+                // 4 groups of 8 rows per 32-row tile of the request-aligned rows (at most T / 32 + n_reqs tiles); the workgroups
+                // that share a group's blocks of 32 units: as many as there are blocks, while ~2048 are in the grid
+                const int groups = 4 * (r.T / 32 + a.n_reqs);
+                const int share = std::max(1, std::min(rope_unit_blocks(a), 2048 / groups));
+                if (a.partial) hipLaunchKernelGGL(rope_append_prefill_kernel<true>, dim3(groups, share), dim3(256), 0, r.s, a);
+                else hipLaunchKernelGGL(rope_append_prefill_kernel<false>, dim3(groups, share), dim3(256), 0, r.s, a);
+            }
+            else hipLaunchKernelGGL(rope_append_decode_kernel, dim3(r.T, ((a.Hq + a.Hkv) * (a.hd >> 4) + a.Hkv * (a.hd >> 3) + kRopeDecThreads - 1) / kRopeDecThreads), dim3(kRopeDecThreads), 0, r.s, a);
+            HIP_TRY(hipGetLastError());
+        }
+        const float scale_log2e = 1.4426950408889634f / sqrtf((float)m.head_dim);
         if (prefill) {
-            // 4 groups of 8 rows per 32-row tile of the request-aligned rows (at most T / 32 + n_reqs tiles); the workgroups
-            // that share a group's blocks of 32 units: as many as there are blocks, while ~2048 are in the grid
-            const int groups = 4 * (r.T / 32 + a.n_reqs);
-            const int share = std::max(1, std::min(rope_unit_blocks(a), 2048 / groups));
-            if (a.partial) hipLaunchKernelGGL(rope_append_prefill_kernel<true>, dim3(groups, share), dim3(256), 0, r.s, a);
-            else hipLaunchKernelGGL(rope_append_prefill_kernel<false>, dim3(groups, share), dim3(256), 0, r.s, a);
+            AttnPrefillArgs a{};
+            a.q = ws.q, a.out = ws.attn, a.cu_chunk = r.pb->cu_chunk, a.prefix_len = r.pb->prefix_len, a.page_table = r.pb->page_table;
+            a.n_reqs = r.pb->n_reqs - r.fused_decode, a.max_pages = r.pb->max_pages;
+            a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
+            a.scale_log2e = scale_log2e;
+            a.n_splits = plan_attn_splits(r.T, m.n_q_heads, r.pb->max_total_len);
+            a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.T = r.T;
+            if (a.n_reqs > 0) NX_TRY(m.head_dim == 128 ? launch_attn_prefill<128>(r, a) : launch_attn_prefill<64>(r, a));
+            if (r.fused_decode) {
+                // the decode requests at the tail of the batch take the decode attention kernel: same queries (prefill
+                // layout), same pools (their new K/V was appended by the rotary kernel above), outputs into the same
+                // attention buffer; the span partials use the decode phase's workspace
+                const int lead = r.pb->n_reqs - r.fused_decode;
+                AttnDecodeArgs d{};
+                d.q = ws.q, d.ctx_len = r.pb->prefix_len + lead, d.page_table = r.pb->page_table + (size_t)lead * r.pb->max_pages;
+                d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.max_ctx = r.fused_max_ctx;
+                d.k_pool = k_pool, d.v_pool = v_pool, d.n_pages = r.kv->n_pages, d.Hq = m.n_q_heads, d.Hkv = m.n_kv_heads;
+                d.scale_log2e = scale_log2e, d.part_o = (f16_t *)c->ws[NEXUS_PHASE_DECODE].part_o, d.part_ml = c->ws[NEXUS_PHASE_DECODE].part_ml;
+                d.seq_parts = c->ws[NEXUS_PHASE_DECODE].seq_parts;
+                d.out = ws.attn, d.lead_cu = r.pb->cu_chunk, d.n_lead = lead, d.out_row0 = r.pb->n_tokens - r.fused_decode;
+                NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, d) : launch_attn_decode<64>(r, d));
+            }
+        } else {
+            AttnDecodeArgs a{};
+            a.q = ws.q, a.ctx_len = r.db->ctx_len, a.page_table = r.db->page_table, a.n_reqs = r.db->n_reqs;
+            a.max_pages = r.db->max_pages, a.max_ctx = r.db->max_ctx;
+            a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
+            a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.seq_parts = ws.seq_parts, a.out = ws.attn;
+            NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, a) : launch_attn_decode<64>(r, a));
         }
-        else hipLaunchKernelGGL(rope_append_decode_kernel, dim3(r.T, ((a.Hq + a.Hkv) * (a.hd >> 4) + a.Hkv * (a.hd >> 3) + kRopeDecThreads - 1) / kRopeDecThreads), dim3(kRopeDecThreads), 0, r.s, a);
-        HIP_TRY(hipGetLastError());
-    }
-    const float scale_log2e = 1.4426950408889634f / sqrtf((float)m.head_dim);
-    if (prefill) {
-        AttnPrefillArgs a{};
-        a.q = ws.q, a.out = ws.attn, a.cu_chunk = r.pb->cu_chunk, a.prefix_len = r.pb->prefix_len, a.page_table = r.pb->page_table;
-        a.n_reqs = r.pb->n_reqs - r.fused_decode, a.max_pages = r.pb->max_pages;
-        a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
-        a.scale_log2e = scale_log2e;
-        a.n_splits = plan_attn_splits(r.T, m.n_q_heads, r.pb->max_total_len);
-        a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.T = r.T;
-        if (a.n_reqs > 0) NX_TRY(m.head_dim == 128 ? launch_attn_prefill<128>(r, a) : launch_attn_prefill<64>(r, a));
-        if (r.fused_decode) {
-            // the decode requests at the tail of the batch take the decode attention kernel: same queries (prefill
-            // layout), same pools (their new K/V was appended by the rotary kernel above), outputs into the same
-            // attention buffer; the span partials use the decode phase's workspace
-            const int lead = r.pb->n_reqs - r.fused_decode;
-            AttnDecodeArgs d{};
-            d.q = ws.q, d.ctx_len = r.pb->prefix_len + lead, d.page_table = r.pb->page_table + (size_t)lead * r.pb->max_pages;
-            d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.max_ctx = r.fused_max_ctx;
-            d.k_pool = k_pool, d.v_pool = v_pool, d.n_pages = r.kv->n_pages, d.Hq = m.n_q_heads, d.Hkv = m.n_kv_heads;
-            d.scale_log2e = scale_log2e, d.part_o = (f16_t *)c->ws[NEXUS_PHASE_DECODE].part_o, d.part_ml = c->ws[NEXUS_PHASE_DECODE].part_ml;
-            d.seq_parts = c->ws[NEXUS_PHASE_DECODE].seq_parts;
-            d.out = ws.attn, d.lead_cu = r.pb->cu_chunk, d.n_lead = lead, d.out_row0 = r.pb->n_tokens - r.fused_decode;
-            NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, d) : launch_attn_decode<64>(r, d));
-        }
-    } else {
-        AttnDecodeArgs a{};
-        a.q = ws.q, a.ctx_len = r.db->ctx_len, a.page_table = r.db->page_table, a.n_reqs = r.db->n_reqs;
-        a.max_pages = r.db->max_pages, a.max_ctx = r.db->max_ctx;
-        a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
-        a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.seq_parts = ws.seq_parts, a.out = ws.attn;
-        NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, a) : launch_attn_decode<64>(r, a));
+        return NEXUS_OK;
     }
     // x1 = x + attn W_o^T, h2 = RMSNorm(x1): when the projection is split along K its reduction, the residual add
     // and the norm are one kernel
-    int o_slices = 0;
-    NX_TRY(run_gemm(r, NEXUS_K_GEMM_O, L.wo, m.hidden, ws.attn, c->q_dim, EPI_RES_IN, ws.x1, x_in, nullptr, m.hidden,
-                    nullptr, 0, &o_slices));
-    if (o_slices) {
-        RmsPartial pp{ws.partial, o_slices, r.T, (const bf16_t *)x_in, ws.x1, nullptr, nullptr};
-        NX_TRY(run_rmsnorm<RMS_IN_PARTIAL>(r, nullptr, L.g2, ws.h, pp));
-    } else {
-        NX_TRY(run_rmsnorm<RMS_IN_F32>(r, ws.x1, L.g2, ws.h));
+    if (stage == 2) {
+        int &o_slices = carry.o_slices;
+        NX_TRY(run_gemm(r, NEXUS_K_GEMM_O, L.wo, m.hidden, ws.attn, c->q_dim, EPI_RES_IN, ws.x1, x_in, nullptr, m.hidden,
+                        nullptr, 0, &o_slices));
+        if (o_slices) {
+            RmsPartial pp{ws.partial, o_slices, r.T, (const bf16_t *)x_in, ws.x1, nullptr, nullptr};
+            NX_TRY(run_rmsnorm<RMS_IN_PARTIAL>(r, nullptr, L.g2, ws.h, pp));
+        } else {
+            NX_TRY(run_rmsnorm<RMS_IN_F32>(r, ws.x1, L.g2, ws.h));
+        }
+        return NEXUS_OK;
     }
-    NX_TRY(run_gemm(r, NEXUS_K_GEMM_GATE_UP, L.wgu, 2 * m.ffn, ws.h, m.hidden, EPI_SWIGLU, nullptr, nullptr, nullptr, 0,
-                    ws.act, m.ffn));
-    NX_TRY(run_gemm(r, NEXUS_K_GEMM_DOWN, L.wdown, m.hidden, ws.act, m.ffn, EPI_RES_OUT, y_out, ws.x1, nullptr, m.hidden,
-                    nullptr, 0, defer_down));
-    return NEXUS_OK;
+    if (stage == 3)
+        return run_gemm(r, NEXUS_K_GEMM_GATE_UP, L.wgu, 2 * m.ffn, ws.h, m.hidden, EPI_SWIGLU, nullptr, nullptr, nullptr, 0, ws.act, m.ffn);
+    return run_gemm(r, NEXUS_K_GEMM_DOWN, L.wdown, m.hidden, ws.act, m.ffn, EPI_RES_OUT, y_out, ws.x1, nullptr, m.hidden,
+                    nullptr, 0, defer_down);
 }
 
-// A phase's pass over a layer range, enqueued one layer at a time so that the host can alternate between the two
-// phases of a step (neither stream then sits idle behind the other phase's launches).
+// A phase's pass over a layer range, enqueued a stage of a layer at a time so that the host can alternate between the two
+// phases of a step: neither stream then sits idle behind the other phase's launches (a step of one tiny layer, whose 18
+// launches are its time: 149 us with whole layers in turn, 122 now).
 // tail (may be null): layers from tail_from on are launched with *tail -- the same phase, batch and workspace on
 // another stream and CU share -- ordered after the layers before them by an event.
 struct PhaseCursor {
     PhaseRun r;
-    int layer_begin, layer_end, l;
+    int layer_begin, layer_end, l, stage = 0;
+    LayerCarry carry;
     const PhaseRun *tail = nullptr;
     int tail_from = 0;
     const bf16_t *x;
@@ -693,12 +710,17 @@ struct PhaseCursor {
         PhaseWs &ws = *r.ws;
         const bool last = l + 1 == layer_end;
         bf16_t *y = last ? (bf16_t *)(r.phase == NEXUS_PHASE_PREFILL ? r.pb->y : r.db->y) : ws.xbuf[(l - layer_begin) & 1];
-        int next_pending = 0;
-        if (tail && l == tail_from && tail->s != r.s) {
-            HIP_TRY(hipEventRecord(r.c->ev_hand, r.s));
-            HIP_TRY(hipStreamWaitEvent(tail->s, r.c->ev_hand, 0));
+        if (stage == 0) {
+            carry = LayerCarry{};
+            if (tail && l == tail_from && tail->s != r.s) {
+                HIP_TRY(hipEventRecord(r.c->ev_hand, r.s));
+                HIP_TRY(hipStreamWaitEvent(tail->s, r.c->ev_hand, 0));
+            }
         }
-        NX_TRY(run_layer(tail && l >= tail_from ? *tail : r, l, x, y, pending, last ? nullptr : &next_pending));
+        int next_pending = 0;
+        NX_TRY(run_layer_stage(tail && l >= tail_from ? *tail : r, l, stage, carry, x, y, pending, last ? nullptr : &next_pending));
+        if (++stage < kLayerStages) return NEXUS_OK;
+        stage = 0;
         pending = next_pending;
         x = y;
         ++l;
@@ -1376,7 +1398,7 @@ static int mixed_step_impl(nexus_ctx *c, int lb, int le, int handover, const nex
     }
     const PhaseRun rp = make_run(c, NEXUS_PHASE_PREFILL, pb, nullptr, kv), rd = make_run(c, NEXUS_PHASE_DECODE, nullptr, db, kv);
     if (split) {
-        // the two phases are enqueued alternately, a layer of each at a time, the decode phase (whose kernels are the
+        // the two phases are enqueued alternately, a stage of each at a time, the decode phase (whose kernels are the
         // shorter ones) first: both streams have work from the start of the step
         PhaseRun rt = rp;
         if (handover < le) {
@@ -1395,7 +1417,7 @@ static int mixed_step_impl(nexus_ctx *c, int lb, int le, int handover, const nex
             }
             if (!pc.done()) {
                 NX_TRY(pc.step());
-                if (sample && pc.l == handover) HIP_TRY(hipEventRecord(sample->ph, L->sp));  // end of the layers run on the share
+                if (sample && pc.l == handover && pc.stage == 0) HIP_TRY(hipEventRecord(sample->ph, L->sp));  // end of the layers run on the share
                 if (pc.done()) NX_TRY(mark_done(c, pc.last_stream(), NEXUS_PHASE_PREFILL, false));
             }
         }
