@@ -251,9 +251,12 @@ static const TileShape *choose_tile(int n_ttiles, int n_ftiles, int Kp, int kste
 // Depends on the problem only (never on the CU share): S fixes the summation order, so results are bit-identical
 // across layouts.  Decode GEMMs are cut along K until there are about 200 workgroups (800 wavefronts, each
 // with its own weight stream in flight); measured on MI355X, more slices cost more in partial-sum traffic than
-// they gain.  Beyond 128 tokens S is the one with the least estimated time of GEMM and partial sums: these cost 0.29 us
-// per MB to write and to read back (the kernel that sums them reads S slices of fp32 where it would have read one of
-// half), and a reduce kernel of its own where no later kernel sums them in passing.
+// they gain.  Beyond 128 tokens S is the one with the least estimated time of GEMM and partial sums.  A second slice
+// costs 0.29 us per MB to write and to read back (the kernel that sums them reads S slices of fp32 where it would have
+// read one of half); every further one is charged 0.7, because a step's other phase pays for it too: with four slices of
+// the down projection instead of two (512 tokens of the 8B shape: 60 against 71 us by itself, the prefill step 1179
+// against 1193) the decode phase next to it on 64 CUs, which bounds the step, slows it from 1946 to 2000.  A reduce
+// kernel of its own, where no later kernel sums the slices in passing, adds 5 us.
 static GemmPlan plan_gemm(int T, int n_ftiles, int Kp, bool own_reduce) {
     const int ksteps = Kp / kGemmBK;
     const int nt = (T + 31) / 32;
@@ -273,7 +276,7 @@ static GemmPlan plan_gemm(int T, int n_ftiles, int Kp, bool own_reduce) {
         for (int s = 1; s <= kMaxTileSlices && ksteps / s >= 8; ++s) {
             double us;
             choose_tile(nt, n_ftiles, Kp, (ksteps + s - 1) / s, s, kChipCUs, &us);
-            if (s > 1) us += (4 * s - 2) * 32.0 * nt * 32.0 * n_ftiles * 0.29e-6 + (own_reduce ? 5.0 : 0.0);
+            if (s > 1) us += (6 * 0.29e-6 + 4 * (s - 2) * 0.7e-6) * 32.0 * nt * 32.0 * n_ftiles + (own_reduce ? 5.0 : 0.0);
             if (s == 1 || us < best) best = us, S = s;
         }
     }
