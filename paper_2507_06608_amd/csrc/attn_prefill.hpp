@@ -1,9 +1,9 @@
 // Chunked-prefill attention (Eq. 4 with the causal bound): every chunk row at absolute position pos attends to
 // keys 0..pos of its request -- the cached prefix and the causal part of the chunk -- read through the page table.
 //
-// One workgroup serves 32*SPB chunk tokens of one request for all G query heads of one KV head, so each K/V page
-// is fetched once per KV head and shared by G*SPB wavefronts through LDS.  Each wavefront owns a 32-token strip of
-// one query head and works on the transposed problem:
+// A workgroup is NW wavefronts, each with a 32-token strip of one query head, that share the K/V pages of one request and
+// kv head through LDS: the (strip, head) pairs of a request and kv head, strip by strip, are cut into runs of NW.  A
+// wavefront works on the transposed problem:
 //     S^T[keys][tokens] = K * Q^T          (v_mfma_f32_32x32x16_bf16; K tile is operand A, Q^T operand B)
 //     O^T[hd][tokens]  += V^T * P^T        (V^T operand A, P^T operand B)
 // In that orientation a lane owns one token column: the softmax running max / sum are per-lane scalars, and the
@@ -28,7 +28,7 @@ struct AttnPrefillArgs {
     const bf16_t *q;  // P32 [request-aligned rows][Hq*hd]
     f16_t *out;       // half, P32 [global token rows][Hq*hd] (operand of the output projection)
     const int32_t *cu_chunk, *prefix_len, *page_table;
-    int n_reqs, max_pages, tiles_per_req;  // tiles of 32*SPB tokens sized from the max_chunk hint
+    int n_reqs, max_pages, tiles_per_req;  // runs of NW (strip, head) pairs of a kv head, sized from the max_chunk hint
     const bf16_t *k_pool, *v_pool;
     int n_pages, Hq, Hkv;
     float scale_log2e;  // log2(e) / sqrt(hd)
@@ -59,9 +59,20 @@ constexpr float kAttnLazyLog2 = 8.f;  // rise of a row's running maximum (log2 u
 constexpr int attn_ahead(int n_waves) { return n_waves > 4 ? 3 : 1; }
 constexpr int attn_stages(int n_waves) { return attn_ahead(n_waves) + 3; }
 
-template <int HD, int G, int SPB>
-__global__ __launch_bounds__(64 * G * SPB, 2) void attn_prefill_kernel(AttnPrefillArgs a) {  // two wavefronts per SIMD
-    constexpr int NW = G * SPB;
+// Wavefronts per workgroup: the registers allow two per SIMD, eight per CU.  Four to a workgroup and two workgroups per CU
+// (eight and one for G = 8, whose heads then share their pages); with one strip of all heads per workgroup G = 5 had five
+// wavefronts on a CU where eight fit (five ragged chunks of the 14B shape, 1021 tokens over prefixes up to 4000: 108 -> 88 us).
+constexpr int attn_waves(int G) { return G == 8 ? 8 : 4; }
+// tokens [0, end) of its request that some pair of run `run` reaches
+template <int G>
+__device__ __forceinline__ int attn_run_end(int run, int n_tokens) {
+    constexpr int NW = attn_waves(G);
+    return min(((run * NW + NW - 1) / G + 1) * 32, n_tokens);
+}
+
+template <int HD, int G>
+__global__ __launch_bounds__(64 * attn_waves(G), 2) void attn_prefill_kernel(AttnPrefillArgs a) {  // two wavefronts per SIMD
+    constexpr int NW = attn_waves(G);
     constexpr int BLK = kPage * HD * 2;      // bytes of one (page, kv head) block
     constexpr int UPB = BLK / 1024;          // 1 KiB units per block
     constexpr int STAGE = 4 * BLK;           // 2 K pages + 2 V pages = 32 keys
@@ -77,24 +88,22 @@ __global__ __launch_bounds__(64 * G * SPB, 2) void attn_prefill_kernel(AttnPrefi
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: branches on it are scalar branches
-    const int hg = w % G, strip = w / G;
     const int g = lane >> 5, col = lane & 31;
     // The kv head is the fastest grid index: workgroups are dealt to the 8 XCDs round-robin, so with 8 kv heads
     // every query tile of a kv head runs on the same XCD and that head's K/V pages are fetched into one L2 instead
     // of all eight (with the tile index fastest, the 16 tiles of the benchmark chunk fetched 83 MB for 8 MB of K/V).
-    const int kvh = blockIdx.x, z = blockIdx.z;
-    const int r = blockIdx.y / a.tiles_per_req;
-    const int lt = a.tiles_per_req - 1 - blockIdx.y % a.tiles_per_req;  // longest-running tiles first
+    const int kvh = blockIdx.x % a.Hkv, z = blockIdx.z, rr = blockIdx.x / a.Hkv;
+    const int r = rr / a.tiles_per_req;
+    const int run = a.tiles_per_req - 1 - rr % a.tiles_per_req;  // longest-running first
+    const int hg = (run * NW + w) % G, st = (run * NW + w) / G;  // this wave's head and 32-token strip inside the request
     const int c0 = a.cu_chunk[r], n_r = a.cu_chunk[r + 1] - c0;
-    if (lt * 32 * SPB >= n_r) return;
+    if (run * NW / G * 32 >= n_r) return;
     int tile_base = 0;
     for (int i = 0; i < r; ++i) tile_base += (a.cu_chunk[i + 1] - a.cu_chunk[i] + 31) >> 5;
     const int prefix = a.prefix_len[r];
     const int32_t *pt = a.page_table + (size_t)r * a.max_pages;
 
-    int blk_last = (lt + 1) * 32 * SPB;
-    if (blk_last > n_r) blk_last = n_r;
-    const int kmax = prefix + blk_last;            // keys [0, kmax) are visible to some row of this block
+    const int kmax = prefix + attn_run_end<G>(run, n_r);  // keys [0, kmax) are visible to some row of this block
     const int n_kv_tiles = (kmax + kAttnTile - 1) / kAttnTile;
     int pages_valid = (kmax + 15) >> 4;
     if (pages_valid > a.max_pages) pages_valid = a.max_pages;
@@ -103,7 +112,6 @@ __global__ __launch_bounds__(64 * G * SPB, 2) void attn_prefill_kernel(AttnPrefi
     attn_split_range(n_kv_tiles, a.n_splits, z, t_begin, t_end);
     if (t_begin >= t_end) return;  // the merge kernel applies the same rule and never reads this split
 
-    const int st = lt * SPB + strip;               // this wave's 32-token strip inside the request
     const bool wave_active = st * 32 < n_r;
     const int local = st * 32 + col;
     const bool tok_ok = wave_active && local < n_r;
@@ -435,7 +443,7 @@ __global__ __launch_bounds__(64 * G * SPB, 2) void attn_prefill_kernel(AttnPrefi
 // the 14B shape 20.0; now 7.0 and 8.5.
 constexpr int kAttnMaxSplits = 8;   // upper bound of the key-range split count (the merge unrolls over it)
 constexpr int kMergeRows = 8, kMergeCols = 256;
-template <int HD, int SPB>
+template <int HD, int G>
 __global__ __launch_bounds__(256) void attn_prefill_merge_kernel(AttnPrefillArgs a, int n_rows) {
     const int t = blockIdx.x * kMergeRows + (threadIdx.x & 7), k = blockIdx.y * kMergeCols + (threadIdx.x >> 3) * 8;
     if (t >= n_rows || k >= a.Hq * HD) return;
@@ -454,8 +462,8 @@ __global__ __launch_bounds__(256) void attn_prefill_merge_kernel(AttnPrefillArgs
         const int b = a.cu_chunk[i], e = a.cu_chunk[i + 1], p = a.prefix_len[i];
         if (b <= t) c0 = b, c1 = e, prefix = p;
     }
-    const int blk_last = min(((t - c0) / (32 * SPB) + 1) * 32 * SPB, c1 - c0);
-    const int n_kv_tiles = (prefix + blk_last + kAttnTile - 1) / kAttnTile;
+    const int run = ((t - c0) / 32 * G + hq % G) / attn_waves(G);
+    const int n_kv_tiles = (prefix + attn_run_end<G>(run, c1 - c0) + kAttnTile - 1) / kAttnTile;
     int ran = 0;  // splits that the main kernel ran for this token (they are contiguous from split 0)
 #pragma unroll
     for (int z = 0; z < kAttnMaxSplits; ++z) {

@@ -514,35 +514,36 @@ static int launch_attn_prefill(const PhaseRun &r, const AttnPrefillArgs &base) {
     nexus_ctx *c = r.c;
     const int G = c->m.n_q_heads / c->m.n_kv_heads;
     AttnPrefillArgs a = base;
-#define NX_ATTN_CASE(GG, SPB)                                                                                        \
+#define NX_ATTN_CASE(GG)                                                                                             \
     case GG: {                                                                                                       \
-        auto kern = attn_prefill_kernel<HD, GG, SPB>;                                                                \
-        constexpr int smem = attn_stages(GG * SPB) * 4 * kPage * HD * 2 + kAttnMaxPages * 4;                         \
+        auto kern = attn_prefill_kernel<HD, GG>;                                                                     \
+        constexpr int smem = attn_stages(attn_waves(GG)) * 4 * kPage * HD * 2 + kAttnMaxPages * 4;                         \
         static bool done = false;                                                                                    \
         if (!done) {                                                                                                 \
             HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));      \
             done = true;                                                                                             \
         }                                                                                                            \
-        a.tiles_per_req = (r.pb->max_chunk + 32 * SPB - 1) / (32 * SPB);                                             \
-        if ((long)a.n_reqs * a.tiles_per_req > 65535) return fail(NEXUS_ESHAPE, "prefill attention grid too large (%d requests x %d tiles)", a.n_reqs, a.tiles_per_req); \
+        const int strips = (r.pb->max_chunk + 31) / 32;                                                              \
+        a.tiles_per_req = (strips * GG + attn_waves(GG) - 1) / attn_waves(GG);                                       \
+        if ((long)a.n_reqs * std::min(a.tiles_per_req, strips) > 65535) return fail(NEXUS_ESHAPE, "prefill attention grid too large (%d requests x %d tiles)", a.n_reqs, a.tiles_per_req); \
         {                                                                                                            \
             Tracer tr(c, r.phase, NEXUS_K_ATTN_PREFILL, r.s);                                                        \
-            hipLaunchKernelGGL(kern, dim3(c->m.n_kv_heads, a.n_reqs * a.tiles_per_req, a.n_splits), dim3(64 * GG * SPB), smem, r.s, a); \
+            hipLaunchKernelGGL(kern, dim3(c->m.n_kv_heads * a.n_reqs * a.tiles_per_req, 1, a.n_splits), dim3(64 * attn_waves(GG)), smem, r.s, a); \
         }                                                                                                            \
         HIP_TRY(hipGetLastError());                                                                                  \
         if (a.n_splits > 1) {                                                                                        \
             Tracer tr(c, r.phase, NEXUS_K_ATTN_MERGE, r.s);                                                          \
             const int rows = r.T - r.fused_decode; /* decode rows of a fused batch are not this kernel's */              \
-            hipLaunchKernelGGL((attn_prefill_merge_kernel<HD, SPB>), dim3((rows + kMergeRows - 1) / kMergeRows, (c->m.n_q_heads * HD + kMergeCols - 1) / kMergeCols), dim3(256), 0, r.s, a, rows); \
+            hipLaunchKernelGGL((attn_prefill_merge_kernel<HD, GG>), dim3((rows + kMergeRows - 1) / kMergeRows, (c->m.n_q_heads * HD + kMergeCols - 1) / kMergeCols), dim3(256), 0, r.s, a, rows); \
         }                                                                                                            \
         break;                                                                                                       \
     }
     switch (G) {
-        NX_ATTN_CASE(1, 4)
-        NX_ATTN_CASE(2, 2)
-        NX_ATTN_CASE(4, 1)
-        NX_ATTN_CASE(5, 1)
-        NX_ATTN_CASE(8, 1)
+        NX_ATTN_CASE(1)
+        NX_ATTN_CASE(2)
+        NX_ATTN_CASE(4)
+        NX_ATTN_CASE(5)
+        NX_ATTN_CASE(8)
         default: return fail(NEXUS_ESHAPE, "query/kv head ratio %d has no prefill attention kernel (1, 2, 4, 5, 8)", G);
     }
 #undef NX_ATTN_CASE
