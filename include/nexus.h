@@ -237,14 +237,14 @@ int nexus_decode_step(nexus_ctx *ctx, int layer_begin, int layer_end, const nexu
 /*
  * nexus_decode_step for callers that cannot allocate device memory or let a library do so: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and bit-identical
- * results; the phase's workspace (activations, split-K partial sums, attention span partials) is laid out in a
+ * results; the phase's workspace (activations, split-K partial sums, attention partials) is laid out in a
  * static device array of the library instead of the context's own buffers, so the call performs no hipMalloc /
  * hipFree and calls no allocating routine; a small clear kernel (no memset node) zeroes what must start at zero.
- * The array is 40 MiB per GPU, exists from library load to process exit and is shared by every context on that
+ * The array is 48 MiB per GPU, exists from library load to process exit and is shared by every context on that
  * GPU: calls that overlap in time on one GPU race on it (calls of one context are ordered by the decode stream).
  * A step whose workspace does not fit fails with NEXUS_ESHAPE before anything is launched: the need grows with
- * n_reqs x (the split-K partial sums of the widest split projection + the attention's partial
- * results); a hidden-4096 GQA layer takes about 23 MB for 64 requests with contexts up to 4096 and does not fit
+ * n_reqs x (the split-K partial sums of the widest split projection + attention partials
+ * for every 256 keys of the longest context); a hidden-4096 GQA layer takes about 23 MB for 64 requests with contexts up to 4096 and does not fit
  * 256 requests with contexts up to 8192.
  * nexus_debug_fetch does not see this call's buffers.
  */

@@ -38,7 +38,7 @@ using namespace nexus;
 // Workspace of nexus_decode_step_noalloc: device memory that exists from the moment the library is loaded, so the
 // call allocates nothing.  One copy per GPU, shared by every context on that GPU, held until the process ends.  In
 // host code the array's name is only a handle: its device address comes from hipGetSymbolAddress, once per device.
-constexpr size_t kScratchBytes = (size_t)40 << 20;
+constexpr size_t kScratchBytes = (size_t)48 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 static unsigned char *g_scratch_ptr[kMaxDevices] = {};
@@ -251,12 +251,12 @@ static const TileShape *choose_tile(int n_ttiles, int n_ftiles, int Kp, int kste
 // Depends on the problem only (never on the CU share): S fixes the summation order, so results are bit-identical
 // across layouts.  Decode GEMMs are cut along K until there are about 200 workgroups (800 wavefronts, each
 // with its own weight stream in flight); measured on MI355X, more slices cost more in partial-sum traffic than
-// they gain.  Beyond 128 tokens S is the one with the least estimated time of GEMM and partial sums.  A second slice
-// costs 0.29 us per MB to write and to read back (the kernel that sums them reads S slices of fp32 where it would have
-// read one of half); every further one is charged 0.7, because a step's other phase pays for it too: with four slices of
-// the down projection instead of two (512 tokens of the 8B shape: 60 against 71 us by itself, the prefill step 1179
-// against 1193) the decode phase next to it on 64 CUs, which bounds the step, slows it from 1946 to 2000.  A reduce
-// kernel of its own, where no later kernel sums the slices in passing, adds 5 us.
+// they gain.  Beyond 128 tokens S is the one with the least estimated time of GEMM and partial sums.  By itself a phase
+// pays 0.29 us per MB of them, written and read back (the kernel that sums them reads S slices of fp32 where it would have
+// read one of half); they are charged 0.7, because a step's other phase pays for them too: with two slices of the QKV and
+// four of the down projection instead of one and two, a 512-token prefill step of the 8B shape takes 1179 us against 1242,
+// and the decode phase next to it on 64 CUs, which bounds a mixed step, 2033 to 2063 against 1915 to 2003.  A reduce kernel
+// of its own, where no later kernel sums the slices in passing, adds 5 us.
 static GemmPlan plan_gemm(int T, int n_ftiles, int Kp, bool own_reduce) {
     const int ksteps = Kp / kGemmBK;
     const int nt = (T + 31) / 32;
@@ -276,7 +276,7 @@ static GemmPlan plan_gemm(int T, int n_ftiles, int Kp, bool own_reduce) {
         for (int s = 1; s <= kMaxTileSlices && ksteps / s >= 8; ++s) {
             double us;
             choose_tile(nt, n_ftiles, Kp, (ksteps + s - 1) / s, s, kChipCUs, &us);
-            if (s > 1) us += (6 * 0.29e-6 + 4 * (s - 2) * 0.7e-6) * 32.0 * nt * 32.0 * n_ftiles + (own_reduce ? 5.0 : 0.0);
+            if (s > 1) us += (4 * s - 2) * 0.7e-6 * 32.0 * nt * 32.0 * n_ftiles + (own_reduce ? 5.0 : 0.0);
             if (s == 1 || us < best) best = us, S = s;
         }
     }
@@ -1259,7 +1259,10 @@ static size_t carve_decode_ws(const nexus_ctx *c, int T, int max_ctx, bool multi
         ws.xbuf[1] = (bf16_t *)take((size_t)T * m.hidden * 2);
     }
     *zero_bytes = off;
-    const size_t items = max_ctx > kDecWholeCtx ? decode_part_slots(T, m.n_kv_heads) * (m.n_q_heads / m.n_kv_heads) : 0;
+    // The limit of the call counts attention partials for every 256 keys of the longest context (the runs need fewer, but for
+    // the shortest batches): which steps fit does not depend on how the kernel cuts the keys.
+    const size_t runs = max_ctx > kDecWholeCtx ? decode_part_slots(T, m.n_kv_heads) * (m.n_q_heads / m.n_kv_heads) : 0;
+    const size_t items = std::max(runs, (size_t)T * m.n_q_heads * ((max_ctx + 255) / 256));
     ws.seq_parts = (int2 *)take((size_t)T * m.n_kv_heads * sizeof(int2));
     ws.part_o = (float *)take(items * m.head_dim * 2);  // half elements
     ws.part_ml = (float *)take(items * 2 * 4);
