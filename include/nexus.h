@@ -141,7 +141,7 @@ typedef struct {
     const int32_t *ctx_len;      /* device [n_reqs]              */
     const int32_t *page_table;   /* device [n_reqs][max_pages]   */
     int32_t max_pages;
-    int32_t max_ctx;             /* host hint: >= every ctx_len[j] + 1 */
+    int32_t max_ctx;             /* host hint: >= every ctx_len[j] + 1 (keys past the hint, rounded up to 256, are ignored) */
 } nexus_decode_batch;
 
 /* Filled by nexus_mixed_step when requested (the call then waits for the step to finish). */
@@ -445,7 +445,7 @@ typedef struct {
  * The batches of one iteration.  All pointers are host memory owned by the scheduler, valid until its next call.
  * Page tables are [n][max_pages] row-major, -1 past a request's own pages; a request holds exactly the pages
  * covering the positions it will have written when the iteration commits.  The fields map one to one onto
- * nexus_prefill_batch / nexus_decode_batch.
+ * nexus_prefill_batch / nexus_decode_batch, but for decode_max_ctx.
  */
 typedef struct {
     int32_t n_prefill, prefill_tokens;
@@ -459,7 +459,8 @@ typedef struct {
     const int32_t *decode_req;         /* [n_decode] request ids, in pool order             */
     const int32_t *decode_ctx;         /* [n_decode] tokens cached before the step          */
     const int32_t *decode_page_table;
-    int32_t decode_max_pages, decode_max_ctx;
+    int32_t decode_max_pages, decode_max_ctx; /* decode_max_ctx: the largest of decode_ctx; nexus_decode_batch.max_ctx
+                                                 counts the new token too and takes decode_max_ctx + 1 */
     int32_t kv_used_pages, kv_total_pages; /* pages holding tokens / pool size: KV_u of Alg. 1 */
 } nexus_sched_batch;
 

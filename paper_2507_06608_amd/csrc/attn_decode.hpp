@@ -27,6 +27,9 @@ namespace nexus {
 // nothing.  A run is at least two pairs long (one request of 800 keys: spans of 256 keys took 8.5 us, runs of 64 take 6.4),
 // and where 256 keys hold every context a wavefront takes one whole (request, kv head): there is then nothing to merge.
 constexpr int kDecWorkers = 1024, kDecMinPairs = 2, kDecWholeCtx = 256;
+// Keys of a context that a batch with this hint attends to.  The hint is at least every context with its new token; one that
+// is too small (the scheduler states contexts without the new token) costs no keys up to the next multiple of 256.
+inline int decode_ctx_bound(int max_ctx) { return round_up(max_ctx, 256); }
 inline int decode_grid(int n_reqs, int n_kv_heads, int max_ctx) {
     const long seqs = (long)n_reqs * n_kv_heads;
     if (max_ctx <= kDecWholeCtx) return (int)seqs;
@@ -39,7 +42,7 @@ inline size_t decode_part_slots(int n_reqs, int n_kv_heads) { return (size_t)kDe
 struct AttnDecodeArgs {
     const bf16_t *q;  // row-major [B][Hq*hd], rotated
     const int32_t *ctx_len, *page_table;
-    int n_reqs, max_pages, max_ctx;  // max_ctx <= kDecWholeCtx: outputs go straight to `out`
+    int n_reqs, max_pages, max_ctx;  // max_ctx: decode_ctx_bound of the hint; <= kDecWholeCtx: outputs go straight to `out`
     int2 *seq_parts;  // [B][Hkv] (run of the first key, number of partial results), written by the wavefront that holds the first key
     const bf16_t *k_pool, *v_pool;
     int n_pages, Hq, Hkv;
@@ -55,7 +58,7 @@ struct AttnDecodeArgs {
     int n_lead, out_row0;
 };
 
-// Keys of request j (contexts past the hint are cut: the hint bounds the work, the page table its reads), and their pairs.
+// Keys of request j (contexts past the bound are cut: it bounds the work, the page table its reads), and their pairs.
 __device__ __forceinline__ int decode_len(const AttnDecodeArgs &a, int j) {
     const int c = a.ctx_len[min(j, a.n_reqs - 1)];  // no branch around the load: the four of a lane are in flight together
     return j < a.n_reqs ? max(0, min(c + 1, a.max_ctx)) : 0;

@@ -655,7 +655,7 @@ static int run_layer_stage(const PhaseRun &r, int layer, int stage, LayerCarry &
                 const int lead = r.pb->n_reqs - r.fused_decode;
                 AttnDecodeArgs d{};
                 d.q = ws.q, d.ctx_len = r.pb->prefix_len + lead, d.page_table = r.pb->page_table + (size_t)lead * r.pb->max_pages;
-                d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.max_ctx = r.fused_max_ctx;
+                d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.max_ctx = decode_ctx_bound(r.fused_max_ctx);
                 d.k_pool = k_pool, d.v_pool = v_pool, d.n_pages = r.kv->n_pages, d.Hq = m.n_q_heads, d.Hkv = m.n_kv_heads;
                 d.scale_log2e = scale_log2e, d.part_o = (f16_t *)c->ws[NEXUS_PHASE_DECODE].part_o, d.part_ml = c->ws[NEXUS_PHASE_DECODE].part_ml;
                 d.seq_parts = c->ws[NEXUS_PHASE_DECODE].seq_parts;
@@ -665,7 +665,7 @@ static int run_layer_stage(const PhaseRun &r, int layer, int stage, LayerCarry &
         } else {
             AttnDecodeArgs a{};
             a.q = ws.q, a.ctx_len = r.db->ctx_len, a.page_table = r.db->page_table, a.n_reqs = r.db->n_reqs;
-            a.max_pages = r.db->max_pages, a.max_ctx = r.db->max_ctx;
+            a.max_pages = r.db->max_pages, a.max_ctx = decode_ctx_bound(r.db->max_ctx);
             a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
             a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.seq_parts = ws.seq_parts, a.out = ws.attn;
             NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, a) : launch_attn_decode<64>(r, a));

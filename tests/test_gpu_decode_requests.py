@@ -1,0 +1,56 @@
+"""What a decode request's output depends on: its own context, and neither how tight the batch's context hint is nor which
+requests share the batch with it.  All comparisons are bit for bit between two decode steps of the library."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2507_06608_amd import synth
+
+from tests.test_gpu_parity import EXTRA_SHAPES
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = dict(EXTRA_SHAPES, tiny=synth.SHAPES["tiny"])
+
+
+@pytest.fixture(scope="module")
+def nx():
+    from paper_2507_06608_amd import binding
+    binding.lib()
+    return binding
+
+
+class Batch:
+    """Decode requests with the given contexts; `run` makes one step of some of them (in the given order) on fresh pools."""
+
+    def __init__(self, nx, shape, ctx_lens, seed=9):
+        sh = SHAPES[shape]
+        self.nx, self.lens = nx, np.asarray(ctx_lens, np.int32)
+        self.wl = synth.make_workload("requests", sh, seed, chunk_lens=[], prefix_lens=[], decode_ctx=ctx_lens, kv_device="cuda:0")
+        self.ctx = nx.context_for(self.wl)
+        self.ctx.load_layer(0, synth.make_weights(sh, seed))
+
+    def run(self, order=None, lens=None, hint=None):
+        d = self.wl.decode
+        order = list(range(d.n_reqs)) if order is None else order
+        lens = self.lens if lens is None else np.asarray(lens, np.int32)
+        db = self.nx.DevDecode(synth.DecodeBatch(d.x[order], lens[order], d.page_table[order]), self.ctx.device)
+        if hint is not None:
+            db.c.max_ctx = hint
+        db.y.fill_(float("nan"))
+        kv = self.ctx.make_kv(self.wl.k_pool, self.wl.v_pool)
+        torch.cuda.synchronize()
+        self.ctx.decode_step(db, kv)
+        self.ctx.sync()
+        assert torch.isfinite(db.y.float()).all()
+        return db.y.view(torch.int16).clone()
+
+
+@pytest.mark.parametrize("lens", [[300, 40, 299], [254, 200, 31], [767, 511, 700, 32]], ids=["301 keys", "255 keys", "768 keys"])
+def test_a_hint_one_short_keeps_the_newest_key(nx, lens):
+    """The scheduler's batch states the largest context without the new token, one less than a step's hint.  Up to the next
+    multiple of 256 a step has always attended to every key of a context that passes its hint, and still does."""
+    print(f"[case] hint one short, {lens}", flush=True)
+    b = Batch(nx, "gqa4", lens)
+    assert torch.equal(b.run(hint=max(lens)), b.run(hint=max(lens) + 1))
+    b.ctx.close()
