@@ -1,11 +1,12 @@
 // Paged grouped-query decode attention (Sec. 2.3: one query token per request against all of its cached keys; a
 // memory-bound sweep over the KV cache), split over the context, plus the merge of the split results.
 //
-// The keys of the batch, laid out request by request, kv head by kv head, are cut into runs of equal length (in pairs
-// of pages, 32 keys) and every run is one wavefront's, whatever requests and heads it touches: ragged contexts leave
-// no wavefront with more to do than another.  The cut is a function of the batch alone, so the reduction order is the
-// same on any CU share.  The wavefront serves all G query heads of its kv head at once, so every K/V byte is fetched
-// once per kv head.  K and V pages are read straight from global memory into MFMA operand registers: the private page
+// A request's keys are cut into spans by a rule on its own context (and on whether the batch is a small one), and a span is
+// reduced by one wavefront from its first key to its last: a request's result does not depend on which requests share the
+// batch, on how tight the context hint is or on the CU share.  The spans of the batch, request by request, kv head by kv
+// head, are dealt to the wavefronts in runs of equal length, whatever requests and heads a run touches: ragged contexts
+// leave no wavefront with much more to do than another.  The wavefront serves all G query heads of its kv head at once, so every
+// K/V byte is fetched once per kv head.  K and V pages are read straight from global memory into MFMA operand registers: the private page
 // layouts make each load instruction cover contiguous runs of memory with 16 bytes per lane, and no LDS is needed because
 // nothing is shared between wavefronts.  S^T = K Q^T and O^T += V^T P^T with the 16x16x32 bf16 MFMA: one column per
 // query head, softmax running max / sum kept per column, and the score registers of two consecutive 16-row tiles
@@ -18,15 +19,41 @@
 
 namespace nexus {
 
-// Wavefronts the keys are dealt to: one per SIMD of the chip, so that all run at once and end together.  A wavefront
+// Wavefronts the spans are dealt to: one per SIMD of the chip, so that all run at once and end together.  A wavefront
 // pays a fixed chain of latencies (context lengths, page ids, first pages: 3 us on an idle chip, 7 us in the queue of a
-// loaded one) per stretch of one request's keys, and a partial result per stretch is written and merged; runs of equal
-// length have few of either.  256 requests with contexts up to 8192: fixed spans of 256 / 1024 keys 815 / 764 us, 512 /
-// 1024 / 2048 / 4096 equal runs 757 / 733 / 746 / 751 us (6.5 TB/s; plain reads of such a size reach 7.0); 64 requests up
-// to 4096 on 64 CUs next to a prefill phase 231 -> 212.  Three or four pairs in flight per wavefront instead of two gain
-// nothing.  A run is at least two pairs long (one request of 800 keys: spans of 256 keys took 8.5 us, runs of 64 take 6.4),
-// and where 256 keys hold every context a wavefront takes one whole (request, kv head): there is then nothing to merge.
+// loaded one) per stretch of one request's keys; runs of equal length have few of them.  256 requests with contexts up to
+// 8192, 8B shape: a wavefront per 256-key span 815 us, runs 768 (512, 2048 and 4096 of them instead of 1024: 2 to 3 % more);
+// without regard to spans, cut at any pair, runs took 750, but then a request's cuts, and its rounding, follow from its
+// neighbours' contexts.  Three or four pairs in flight per wavefront instead of two gain nothing.
+//
+// Spans, in pairs of pages (32 keys).  Where 256 keys hold a context it is one span, and nothing is to be merged.  Otherwise a
+// long span costs balance (a run is longer or shorter by up to one) and parallelism (a batch of few requests has fewer
+// spans than the chip has SIMDs), a short one costs stores and merging.  Up to 32 requests: 2 pairs up to 1024 keys (one
+// request of 800 keys, 8B shape: 6.4 us; 8 pairs 8.5), 4 up to 4096 (23 requests up to 2500, a step of four layers of the 14B
+// shape: 601 us, 604 with 2 pairs up to 2048), 8 beyond (one of 8000, a step of two layers: 233 us, 246 with 2 pairs).  More
+// requests: 8 pairs (64 up to 4096: 828 us for a step of four layers, 830 with 4 pairs), and 16 beyond 4096 keys if there are
+// more than 64 (the 256 requests above 768 us, 781 with 8 pairs).  The bounds 32 and 64 are those at which the projections
+// change their order of summation, too.
 constexpr int kDecWorkers = 1024, kDecMinPairs = 2, kDecWholeCtx = 256;
+// log2 of the pairs of pages in a span of a context of `len` keys; decode_spans: its spans
+__host__ __device__ __forceinline__ int decode_span_shift(int n_reqs, int len) {
+    if (len <= kDecWholeCtx) return 3;
+    if (n_reqs > 64 && len > 4096) return 4;
+    if (n_reqs > 32 || len > 4096) return 3;
+    return len > 1024 ? 2 : 1;
+}
+__host__ __device__ __forceinline__ int decode_pairs(int len) { return (len + 31) >> 5; }
+__host__ __device__ __forceinline__ int decode_spans(int n_reqs, int len) {
+    const int sh = decode_span_shift(n_reqs, len);
+    return (decode_pairs(len) + (1 << sh) - 1) >> sh;
+}
+// Largest number of spans of a context of at most max_ctx keys.
+inline int decode_max_spans(int n_reqs, int max_ctx) {
+    int n = decode_spans(n_reqs, max_ctx);
+    for (int top : {kDecWholeCtx, 1024, 4096})
+        if (max_ctx > top) n = std::max(n, decode_spans(n_reqs, top));
+    return n;
+}
 // Keys of a context that a batch with this hint attends to.  The hint is at least every context with its new token; one that
 // is too small (the scheduler states contexts without the new token) costs no keys up to the next multiple of 256.
 inline int decode_ctx_bound(int max_ctx) { return round_up(max_ctx, 256); }
@@ -36,19 +63,17 @@ inline int decode_grid(int n_reqs, int n_kv_heads, int max_ctx) {
     const long runs = (seqs * ((max_ctx + 31) / 32) + kDecMinPairs - 1) / kDecMinPairs;
     return (int)(runs < kDecWorkers ? runs : kDecWorkers);
 }
-// Partial results of a batch: each is the first of its run or the first of its (request, kv head).
-inline size_t decode_part_slots(int n_reqs, int n_kv_heads) { return (size_t)kDecWorkers + (size_t)n_reqs * n_kv_heads; }
 
 struct AttnDecodeArgs {
     const bf16_t *q;  // row-major [B][Hq*hd], rotated
     const int32_t *ctx_len, *page_table;
     int n_reqs, max_pages, max_ctx;  // max_ctx: decode_ctx_bound of the hint; <= kDecWholeCtx: outputs go straight to `out`
-    int2 *seq_parts;  // [B][Hkv] (run of the first key, number of partial results), written by the wavefront that holds the first key
+    int max_spans;  // decode_max_spans of max_ctx
     const bf16_t *k_pool, *v_pool;
     int n_pages, Hq, Hkv;
     float scale_log2e;
-    f16_t *part_o;   // [run + (request, kv head)][G][hd]: each stretch's output normalised by its own sum, half
-    float *part_ml;  // [run + (request, kv head)][G][2]  (running max in the log2 domain, sum)
+    f16_t *part_o;   // [B][Hkv][max_spans][G][hd]: each span's output normalised by its own sum, half
+    float *part_ml;  // [B][Hkv][max_spans][G][2]  (running max in the log2 domain, sum)
     f16_t *out;      // merge output: half, P32 [B rows][Hq*hd]
     // Decode requests riding in a chunked-prefill batch (the fused single-batch step): their queries sit in the
     // prefill layout -- P32, every request on a 32-row boundary, request j of the decode part in the row tile that
@@ -63,7 +88,6 @@ __device__ __forceinline__ int decode_len(const AttnDecodeArgs &a, int j) {
     const int c = a.ctx_len[min(j, a.n_reqs - 1)];  // no branch around the load: the four of a lane are in flight together
     return j < a.n_reqs ? max(0, min(c + 1, a.max_ctx)) : 0;
 }
-__device__ __forceinline__ int decode_pairs(int len) { return (len + 31) >> 5; }
 
 // Inclusive sum over the lanes of a wavefront, by lane moves of the vector ALU (no trip through LDS).
 __device__ __forceinline__ int wave_inclusive_sum(int v) {
@@ -81,13 +105,21 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
     constexpr int KK = HD / 32;   // k-steps of QK^T
     constexpr int RT = HD / 16;   // 16-row tiles of O^T
     constexpr int BLK = kPage * HD;  // elements per (page, kv head) block
+    // Results of finished spans, written out at the end of the run or when the stage is full (17 KB at most: eight
+    // wavefronts of a CU fit).  A store counts like a load, and the loads behind it are waited for in order: the 256 requests
+    // above, in spans of 8 pairs, took 821 us with every result stored between the pairs, 808 staged per request and kv
+    // head, 781 staged per run (731 with the stores left out).
+    constexpr int kStage = 64 / G < 16 ? 64 / G : 16, CPS = G * HD / 8;  // spans, 16-byte chunks of a span
+    __shared__ uint4 stage_o[kStage * CPS];
+    __shared__ float2 stage_ml[kStage * G];
+    __shared__ int stage_slot[kStage];
     const int lane = threadIdx.x & 63;
     const int col = lane & 15, g4 = lane >> 4;
     const int w = blockIdx.x;
 
-    // This wavefront's run: pairs [run_begin, run_begin + todo) of the batch's pairs in (request, kv head) order.  A lane
-    // counts the pairs of 4 consecutive requests, a wavefront scan places 256.
-    int j = 0, kvh = 0, pair = 0, todo = 0, per = 1, run_begin = 0, len = 0;
+    // This wavefront's run: the spans whose first pairs are among the pairs [run_begin, run_begin + per) of the batch's pairs in
+    // (request, kv head) order.  A lane counts the pairs of 4 consecutive requests, a wavefront scan places 256.
+    int j = 0, kvh = 0, pair = 0, todo = 0, len = 0;
     const bool whole = a.max_ctx <= kDecWholeCtx;
     if (whole) {
         j = w / a.Hkv, kvh = w % a.Hkv;
@@ -105,8 +137,8 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
         };
         for (int base = 0; base < a.n_reqs; base += 256) total += scan(base);
         total *= a.Hkv;
-        per = max(kDecMinPairs, (total + kDecWorkers - 1) / kDecWorkers);
-        run_begin = w * per;
+        const int per = max(kDecMinPairs, (total + kDecWorkers - 1) / kDecWorkers);
+        const int run_begin = w * per;
         if (run_begin >= total) return;
         todo = min(per, total - run_begin);
         int before = 0, base = 0;  // pairs of the requests before `base`, then before j
@@ -125,6 +157,8 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
         }
         const int np = decode_pairs(len), rest = run_begin - before;
         kvh = rest / np, pair = rest % np;
+        const int span = 1 << decode_span_shift(a.n_reqs, len), skip = min((span - pair % span) % span, np - pair);
+        pair += skip, todo -= skip;
     }
     j = __builtin_amdgcn_readfirstlane(j), kvh = __builtin_amdgcn_readfirstlane(kvh), len = __builtin_amdgcn_readfirstlane(len);
     pair = __builtin_amdgcn_readfirstlane(pair), todo = __builtin_amdgcn_readfirstlane(todo);
@@ -134,20 +168,30 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
     if (a.lead_cu)
         for (int i = 0; i < a.n_lead; ++i) lead_tiles += (a.lead_cu[i + 1] - a.lead_cu[i] + 31) >> 5;
 
-    // one stretch of a (request, kv head) after another
-    for (int at = run_begin; todo > 0;) {
-    const int np = decode_pairs(len), n_pairs = min(todo, np - pair);
+    int staged = 0;
+    auto write_staged = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // what other lanes wrote
+        for (int i = lane; i < staged * CPS; i += 64) ((uint4 *)a.part_o)[(size_t)stage_slot[i / CPS] * CPS + i % CPS] = stage_o[i];
+        for (int i = lane; i < staged * G; i += 64) ((float2 *)a.part_ml)[(size_t)stage_slot[i / G] * G + i % G] = stage_ml[i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        staged = 0;
+    };
+
+    // one stretch of spans of a (request, kv head) after another
+    while (todo > 0) {
+    const int np = decode_pairs(len), sh = decode_span_shift(a.n_reqs, len), span = 1 << sh;
+    const int n_pairs = min((todo + span - 1) & -span, np - pair);
     if (n_pairs > 0) {
-    // Page ids, 64 at a time, one per lane: no key/value load waits on a page-table read.  Ids that are out of range or
-    // belong to pages past the end of the context are replaced by page 0: every load below then has a valid address and
-    // no branch, and what it fetches for such a page is masked out.
+    // Page ids of a span, one per lane, fetched a span ahead: no key/value load waits on a page-table read.  Ids that are out
+    // of range or belong to pages past the end of the context are replaced by page 0: every load below then has a valid
+    // address and no branch, and what it fetches for such a page is masked out.
     auto page_ids = [&](int lp0) {
         const int lp = lp0 + lane;
         int id = 0;
         if (lp * 16 < len && lp < a.max_pages) id = a.page_table[(size_t)j * a.max_pages + lp];
         return (unsigned)id < (unsigned)a.n_pages ? id : 0;
     };
-    int my_page = page_ids(2 * pair);
+    int ids = page_ids(2 * pair);
 
     const int q_row = (lead_tiles + j) * 32;
     bf16x8 qf[KK];
@@ -174,7 +218,7 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
     struct PairRegs {
         u32x4 k1[KK], k2[KK], v[RT];
     };
-    auto load_pair = [&](PairRegs &r, int ids, int pp) {  // pair pp of the 32 whose page ids are given
+    auto load_pair = [&](PairRegs &r, int ids, int pp) {  // pair pp of the span whose page ids are given
         const int pageA = __builtin_amdgcn_readlane(ids, 2 * pp), pageB = __builtin_amdgcn_readlane(ids, 2 * pp + 1);
         // K operand row (lane % 16): rows 0..7 from page A, 8..15 from page B
         const bf16_t *kp = a.k_pool + ((size_t)(col < 8 ? pageA : pageB) * a.Hkv + kvh) * BLK + half_off;
@@ -241,87 +285,99 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
         }
     };
 
+    // The running span's result, and the start of the next one's.  Register e of o_acc[i] is hd = 16 i + 4 g4 + e.  Stored
+    // normalised (an average of value rows, inside half's range whenever the values are) and in half: half the bytes of an
+    // fp32 partial, at a rounding 4x finer than the bf16 the values came in; a span is never empty.
+    auto sum_lanes = [&]() {
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
+        return 1.0f / l_run;
+    };
+    auto row = [&](int i, float inv_l) {
+        return uint2{packh2(o_acc[i][0] * inv_l, o_acc[i][1] * inv_l), packh2(o_acc[i][2] * inv_l, o_acc[i][3] * inv_l)};
+    };
+    auto stage_span = [&](int s) {
+        const float inv_l = sum_lanes();
+        if (lane == 0) stage_slot[staged] = (j * a.Hkv + kvh) * a.max_spans + s;
+        if (col < G) {
+            f16_t *so = (f16_t *)stage_o + (staged * G + col) * HD + 4 * g4;
+#pragma unroll
+            for (int i = 0; i < RT; ++i) *(uint2 *)(so + 16 * i) = row(i, inv_l);
+            if (g4 == 0) stage_ml[staged * G + col] = float2{m_run, l_run};
+        }
+#pragma unroll
+        for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o_acc[i][e] = 0.f;
+        m_run = -INFINITY, l_run = 0.f;
+        if (++staged == kStage) write_staged();
+    };
+
     // Two register sets: the loads of the next pair are in flight while the current pair is computed.  The steady
     // state loop has no branch around a prefetch: with one, the paths with and without the extra loads in flight
     // merge, and the compiler can only wait as if they had not been issued, i.e. for the prefetch itself.
     PairRegs r0, r1;
-    load_pair(r0, my_page, 0);
-    int done = 0;  // pairs of this stretch behind the window of 32 whose page ids are in my_page
-    for (; n_pairs - done > 32; done += 32) {
-        const int next_page = page_ids(2 * (pair + done + 32));
-        for (int pp = 0; pp < 30; pp += 2) {
-            load_pair(r1, my_page, pp + 1);
-            compute_pair(r0, pair + done + pp);
-            load_pair(r0, my_page, pp + 2);
-            compute_pair(r1, pair + done + pp + 1);
+    load_pair(r0, ids, 0);
+    int p0 = pair;  // first pair of the running span
+    for (; pair + n_pairs - p0 > span; p0 += span) {
+        const int next_ids = page_ids(2 * (p0 + span));
+        load_pair(r1, ids, 1);
+        if (p0 > pair) stage_span((p0 - 1) >> sh);
+        compute_pair(r0, p0);
+        load_pair(r0, span > 2 ? ids : next_ids, span > 2 ? 2 : 0);
+        compute_pair(r1, p0 + 1);
+        for (int pp = 2; pp < span; pp += 2) {
+            load_pair(r1, ids, pp + 1);
+            compute_pair(r0, p0 + pp);
+            load_pair(r0, pp + 2 < span ? ids : next_ids, pp + 2 < span ? pp + 2 : 0);
+            compute_pair(r1, p0 + pp + 1);
         }
-        load_pair(r1, my_page, 31);
-        compute_pair(r0, pair + done + 30);
-        load_pair(r0, next_page, 0);
-        compute_pair(r1, pair + done + 31);
-        my_page = next_page;
+        ids = next_ids;
     }
+    if (p0 > pair) stage_span((p0 - 1) >> sh);
     {
-        const int left = n_pairs - done, p0 = pair + done;
+        const int left = pair + n_pairs - p0;
         int pp = 0;
         for (; pp + 2 < left; pp += 2) {
-            load_pair(r1, my_page, pp + 1);
+            load_pair(r1, ids, pp + 1);
             compute_pair(r0, p0 + pp);
-            load_pair(r0, my_page, pp + 2);
+            load_pair(r0, ids, pp + 2);
             compute_pair(r1, p0 + pp + 1);
         }
         if (pp + 1 < left) {
-            load_pair(r1, my_page, pp + 1);
+            load_pair(r1, ids, pp + 1);
             compute_pair(r0, p0 + pp);
             compute_pair(r1, p0 + pp + 1);
         } else {
             compute_pair(r0, p0 + pp);
         }
     }
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
-    // register e of o_acc[i] is hd = 16 i + 4 g4 + e.  Stored normalised (an average of value rows, inside half's range
-    // whenever the values are) and in half: half the bytes of an fp32 partial, at a rounding 4x finer than the bf16 the
-    // values came in; a stretch is never empty
-    const int seq = j * a.Hkv + kvh;
-    const float inv_l = 1.0f / l_run;
-    uint2 o[RT];
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-        o[i] = uint2{packh2(o_acc[i][0] * inv_l, o_acc[i][1] * inv_l), packh2(o_acc[i][2] * inv_l, o_acc[i][3] * inv_l)};
-    if (!whole && pair == 0 && lane == 0) a.seq_parts[seq] = int2{w, n_pairs == np ? 1 : (at + np - 1) / per - w + 1};
-    if (col < G) {
-        if (n_pairs == np) {  // nothing to merge: the output row itself, P32
+    if (np > span) {
+        stage_span(p0 >> sh);
+    } else {  // a single span, nothing to merge: the output row itself, P32
+        const float inv_l = sum_lanes();
+        if (col < G)
 #pragma unroll
             for (int i = 0; i < RT; ++i)
-                *(uint2 *)(a.out + p32_offset(a.out_row0 + j, (kvh * G + col) * HD + 16 * i + 4 * g4, a.Hq * HD)) = o[i];
-        } else {
-            const size_t item = (size_t)(w + seq) * G + col;
-#pragma unroll
-            for (int i = 0; i < RT; ++i) *(uint2 *)(a.part_o + item * HD + 16 * i + 4 * g4) = o[i];
-            if (g4 == 0) {
-                float2 ml = {m_run, l_run};
-                *(float2 *)(a.part_ml + item * 2) = ml;
-            }
-        }
+                *(uint2 *)(a.out + p32_offset(a.out_row0 + j, (kvh * G + col) * HD + 16 * i + 4 * g4, a.Hq * HD)) = row(i, inv_l);
     }
     }
-    todo -= n_pairs, at += n_pairs, pair = 0;
+    todo -= n_pairs, pair = 0;
     if (++kvh == a.Hkv) kvh = 0, ++j, len = todo > 0 ? __builtin_amdgcn_readfirstlane(decode_len(a, j)) : 0;
     }
+    if (staged) write_staged();
 }
 
 // Merge of the partial results of one (request, query head): with w_s = 2^(m_s - m) l_s and o_s the normalised output of
-// its s-th stretch of keys, o = sum_s w_s o_s / sum_s w_s, in order.  One wavefront per (request, query head); output in
-// P32 order for the O projection.  A request that one wavefront swept whole has its output already.
+// its s-th span, o = sum_s w_s o_s / sum_s w_s, in order.  One wavefront per (request, query head); output in P32 order for
+// the O projection.  A request of a single span has its output already.
 template <int HD, int G>
 __global__ __launch_bounds__(64) void attn_merge_kernel(AttnDecodeArgs a) {
     const int j = blockIdx.x / a.Hq, hq = blockIdx.x % a.Hq;
     const int kvh = hq / G, col = hq % G, lane = threadIdx.x;
-    const int2 parts = a.seq_parts[j * a.Hkv + kvh];
-    const int n_spans = min(parts.y, decode_pairs(decode_len(a, j)));
+    const int n_spans = decode_spans(a.n_reqs, decode_len(a, j));
     if (n_spans <= 1) return;
-    const size_t item0 = (size_t)parts.x + j * a.Hkv + kvh;
+    const size_t item0 = ((size_t)j * a.Hkv + kvh) * a.max_spans;
     constexpr int EPL = HD / 64;
     float acc[EPL], m = -INFINITY, denom = 0.f;
 #pragma unroll

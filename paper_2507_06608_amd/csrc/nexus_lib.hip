@@ -81,7 +81,6 @@ struct PhaseWs {
     float *partial = nullptr;
     size_t partial_elems = 0;
     float *part_o = nullptr, *part_ml = nullptr;  // attention split results
-    int2 *seq_parts = nullptr;                    // decode attention: where a request's split results are
     int q_rows = 0;
 };
 
@@ -658,7 +657,7 @@ static int run_layer_stage(const PhaseRun &r, int layer, int stage, LayerCarry &
                 d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.max_ctx = decode_ctx_bound(r.fused_max_ctx);
                 d.k_pool = k_pool, d.v_pool = v_pool, d.n_pages = r.kv->n_pages, d.Hq = m.n_q_heads, d.Hkv = m.n_kv_heads;
                 d.scale_log2e = scale_log2e, d.part_o = (f16_t *)c->ws[NEXUS_PHASE_DECODE].part_o, d.part_ml = c->ws[NEXUS_PHASE_DECODE].part_ml;
-                d.seq_parts = c->ws[NEXUS_PHASE_DECODE].seq_parts;
+                d.max_spans = decode_max_spans(d.n_reqs, d.max_ctx);
                 d.out = ws.attn, d.lead_cu = r.pb->cu_chunk, d.n_lead = lead, d.out_row0 = r.pb->n_tokens - r.fused_decode;
                 NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, d) : launch_attn_decode<64>(r, d));
             }
@@ -667,7 +666,8 @@ static int run_layer_stage(const PhaseRun &r, int layer, int stage, LayerCarry &
             a.q = ws.q, a.ctx_len = r.db->ctx_len, a.page_table = r.db->page_table, a.n_reqs = r.db->n_reqs;
             a.max_pages = r.db->max_pages, a.max_ctx = decode_ctx_bound(r.db->max_ctx);
             a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
-            a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.seq_parts = ws.seq_parts, a.out = ws.attn;
+            a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.out = ws.attn;
+            a.max_spans = decode_max_spans(a.n_reqs, a.max_ctx);
             NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, a) : launch_attn_decode<64>(r, a));
         }
         return NEXUS_OK;
@@ -886,7 +886,7 @@ void nexus_destroy(nexus_ctx *c) {
     }
     for (auto &w : c->ws) {
         (void)hipFree(w.h), (void)hipFree(w.qkv), (void)hipFree(w.q), (void)hipFree(w.attn), (void)hipFree(w.x1), (void)hipFree(w.act);
-        (void)hipFree(w.xbuf[0]), (void)hipFree(w.xbuf[1]), (void)hipFree(w.partial), (void)hipFree(w.part_o), (void)hipFree(w.part_ml), (void)hipFree(w.seq_parts);
+        (void)hipFree(w.xbuf[0]), (void)hipFree(w.xbuf[1]), (void)hipFree(w.partial), (void)hipFree(w.part_o), (void)hipFree(w.part_ml);
     }
     (void)hipFree(c->rope_tab);
     (void)hipFree(c->probe_counts);
@@ -918,8 +918,9 @@ static int alloc_phase_ws(nexus_ctx *c, int phase, int maxT, int max_reqs) {
         NX_TRY(dev_alloc(&w.part_ml, items * 2, false));
     } else {
         NX_TRY(dev_alloc(&w.q, (size_t)maxT * c->q_dim, true));
-        const size_t items = decode_part_slots(maxT, m.n_kv_heads) * (m.n_q_heads / m.n_kv_heads);
-        NX_TRY(dev_alloc(&w.seq_parts, (size_t)maxT * m.n_kv_heads, true));
+        size_t items = 0;  // spans of the attention: the largest batch of each kind
+        for (int T : {std::min(maxT, 32), std::min(maxT, 64), maxT})
+            items = std::max(items, (size_t)T * m.n_q_heads * decode_max_spans(T, decode_ctx_bound(c->lim.max_positions)));
         NX_TRY(dev_alloc(&w.part_o, (items * m.head_dim + 1) / 2, false));  // half elements
         NX_TRY(dev_alloc(&w.part_ml, items * 2, false));
     }
@@ -1259,11 +1260,8 @@ static size_t carve_decode_ws(const nexus_ctx *c, int T, int max_ctx, bool multi
         ws.xbuf[1] = (bf16_t *)take((size_t)T * m.hidden * 2);
     }
     *zero_bytes = off;
-    // The limit of the call counts attention partials for every 256 keys of the longest context (the runs need fewer, but for
-    // the shortest batches): which steps fit does not depend on how the kernel cuts the keys.
-    const size_t runs = max_ctx > kDecWholeCtx ? decode_part_slots(T, m.n_kv_heads) * (m.n_q_heads / m.n_kv_heads) : 0;
-    const size_t items = std::max(runs, (size_t)T * m.n_q_heads * ((max_ctx + 255) / 256));
-    ws.seq_parts = (int2 *)take((size_t)T * m.n_kv_heads * sizeof(int2));
+    // The limit of the call counts attention partials for every 256 keys of the longest context, or all that are written.
+    const size_t items = (size_t)T * m.n_q_heads * std::max(decode_max_spans(T, decode_ctx_bound(max_ctx)), (max_ctx + 255) / 256);
     ws.part_o = (float *)take(items * m.head_dim * 2);  // half elements
     ws.part_ml = (float *)take(items * 2 * 4);
     const int shapes[4][2] = {{c->n_qkv, m.hidden}, {m.hidden, c->q_dim}, {2 * m.ffn, m.hidden}, {m.hidden, m.ffn}};

@@ -54,3 +54,30 @@ def test_a_hint_one_short_keeps_the_newest_key(nx, lens):
     b = Batch(nx, "gqa4", lens)
     assert torch.equal(b.run(hint=max(lens)), b.run(hint=max(lens) + 1))
     b.ctx.close()
+
+
+# contexts around the 32-key pairs and 256 keys, short and long next to one another
+LENS = [0, 15, 31, 32, 254, 255, 256, 257, 511, 512, 700, 1023, 1024, 1025, 1500, 2047, 2048, 2100, 3000, 4095, 4096, 4200]
+
+
+@pytest.mark.parametrize("shape,n", [("tiny", 22), ("gqa2", 33), ("gqa4", 32), ("gqa5", 64), ("gqa8", 65), ("gqa4", 300)],
+                         ids=["hd 64 G 1, 22", "G 2, 33", "G 4, 32", "G 5, 64", "G 8, 65", "G 4, 300"])
+def test_a_request_does_not_depend_on_its_neighbours(nx, shape, n):
+    """The same requests next to others with other contexts, in another order and under a looser hint: the rows of the
+    requests that stayed the same keep their bits."""
+    print(f"[case] decode neighbours, {shape} {n} requests", flush=True)
+    rng = np.random.default_rng(n)
+    lens = (LENS + rng.integers(0, 3000, max(0, n - len(LENS))).tolist())[:n]
+    b = Batch(nx, shape, lens)
+    ref = b.run()
+    kept = [j for j in range(n) if j % 3 != 1]
+    other = np.asarray(lens, np.int32).copy()
+    for j in range(1, n, 3):
+        other[j] = rng.integers(0, lens[j] + 1)
+    y = b.run(lens=other)
+    assert torch.equal(y[kept], ref[kept]), "other contexts next to it"
+    order = rng.permutation(n).tolist()
+    assert torch.equal(b.run(order=order), ref[order]), "another order"
+    short = [j for j in range(n) if lens[j] < 256]
+    assert torch.equal(b.run(order=short), b.run(order=short, hint=max(lens) + 1)), "a looser hint"
+    b.ctx.close()
