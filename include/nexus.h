@@ -243,9 +243,10 @@ int nexus_decode_step(nexus_ctx *ctx, int layer_begin, int layer_end, const nexu
  * The array is 48 MiB per GPU, exists from library load to process exit and is shared by every context on that
  * GPU: calls that overlap in time on one GPU race on it (calls of one context are ordered by the decode stream).
  * A step whose workspace does not fit fails with NEXUS_ESHAPE before anything is launched: the need grows with
- * n_reqs x (the split-K partial sums of the widest split projection + attention partials
- * for every 256 keys of the longest context); a hidden-4096 GQA layer takes about 23 MB for 64 requests with contexts up to 4096 and does not fit
- * 256 requests with contexts up to 8192.
+ * n_reqs x (the split-K partial sums of the widest split projection + the attention partials of the longest context,
+ * one per 256 keys and query head; per 512 beyond 4096 keys in batches of more than 64, per 64 or 128 up to 4096 keys in
+ * batches of up to 32); a hidden-4096 GQA layer takes about 23 MB for 64 requests with contexts up to 4096 and does not
+ * fit 256 requests with contexts up to 8192.
  * nexus_debug_fetch does not see this call's buffers.
  */
 int nexus_decode_step_noalloc(nexus_ctx *ctx, int layer_begin, int layer_end, const nexus_decode_batch *db,

@@ -1260,8 +1260,7 @@ static size_t carve_decode_ws(const nexus_ctx *c, int T, int max_ctx, bool multi
         ws.xbuf[1] = (bf16_t *)take((size_t)T * m.hidden * 2);
     }
     *zero_bytes = off;
-    // The limit of the call counts attention partials for every 256 keys of the longest context, or all that are written.
-    const size_t items = (size_t)T * m.n_q_heads * std::max(decode_max_spans(T, decode_ctx_bound(max_ctx)), (max_ctx + 255) / 256);
+    const size_t items = (size_t)T * m.n_q_heads * decode_max_spans(T, decode_ctx_bound(max_ctx));
     ws.part_o = (float *)take(items * m.head_dim * 2);  // half elements
     ws.part_ml = (float *)take(items * 2 * 4);
     const int shapes[4][2] = {{c->n_qkv, m.hidden}, {m.hidden, c->q_dim}, {2 * m.ffn, m.hidden}, {m.hidden, m.ffn}};

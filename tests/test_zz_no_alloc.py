@@ -108,3 +108,24 @@ def test_noalloc_decode_step_rejects_what_does_not_fit(nx):
     ctx.sync()
     assert torch.isfinite(db.y.float()).all()
     ctx.close()
+
+
+def test_noalloc_decode_step_takes_what_fits(nx):
+    """The need counts the attention partials that the kernels write and nothing else: 128 requests of 8192 keys fit."""
+    print("[case] no-alloc decode step, 128 requests of 8192 keys", flush=True)
+    sh = synth.SHAPES["llama3_8b"]
+    wl = synth.make_workload("fits", sh, 25, chunk_lens=[], prefix_lens=[], decode_ctx=[8191] * 128, kv_device="cuda:0")
+    ctx = nx.context_for(wl)
+    ctx.load_layer(0, synth.make_weights(sh, 25))
+    kv = ctx.make_kv(wl.k_pool, wl.v_pool)
+    outs = []
+    for call in (ctx.decode_step, ctx.decode_step_noalloc):
+        db = nx.DevDecode(wl.decode, ctx.device)
+        db.y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        call(db, kv)
+        ctx.sync()
+        outs.append(db.y.clone())
+    assert torch.isfinite(outs[1].float()).all()
+    assert torch.equal(_bits(outs[0]), _bits(outs[1]))
+    ctx.close()
