@@ -977,9 +977,11 @@ int nexus_create(const nexus_model_desc *desc, const nexus_limits *limits, int d
         c->bits_xcd_major = order && !strcmp(order, "xcd_major");
         // test hook: one GEMM tile shape (a name of kTileShapes) for every projection of more than 128 tokens, to compare
         // the shapes bit for bit and to time them against each other
-        if (const char *tiles = getenv("NEXUS_GEMM_TILES"))
+        if (const char *tiles = getenv("NEXUS_GEMM_TILES"); tiles && *tiles) {
             for (const TileShape &t : kTileShapes)
                 if (!strcmp(tiles, t.name)) c->force_tile = &t;
+            if (!c->force_tile) { rc = fail(NEXUS_EINVAL, "NEXUS_GEMM_TILES names no tile shape: %s", tiles); break; }
+        }
         if (const char *dbg = getenv("NEXUS_DEBUG_CHECKS")) c->debug_checks = atoi(dbg) != 0;
         if (const char *ml = getenv("NEXUS_MAX_LAYOUTS")) c->max_layouts = std::max(1, std::min(64, atoi(ml)));
         if (hipStreamCreateWithFlags(&c->s_main, hipStreamNonBlocking) != hipSuccess) { rc = fail(NEXUS_EHIP, "stream creation failed"); break; }

@@ -58,3 +58,11 @@ def test_all_tile_shapes_agree(nx, oracle, monkeypatch, shape, chunks):
         assert_close(f"{shape} {chunks}", f32(y), ref["y_p"])
     for tiles in TILES:
         assert torch.equal(run(tiles).view(torch.int16), y.view(torch.int16)), tiles
+
+
+def test_an_unknown_tile_shape_is_refused(nx, monkeypatch):
+    """A name that is no shape would silently compare the default with itself."""
+    print("[case] unknown tile shape", flush=True)
+    monkeypatch.setenv("NEXUS_GEMM_TILES", "128x129")
+    with pytest.raises(nx.NexusError, match="128x129"):
+        nx.Nexus(synth.SHAPES["tiny"], max_prefill_tokens=256, max_prefill_reqs=1, max_decode_reqs=1, max_positions=256)
