@@ -1,16 +1,20 @@
 """Every tile shape of the tiled GEMM against every other, bit for bit: per element they add the same products in the same
 order, so any shape must reproduce a chunk's outputs exactly, with ragged token counts (partial token tiles), widths that
-are no multiple of the tile (partial feature tiles), one to four K slices and K ranges shorter than the widest ring.  One
-of the runs is checked against the oracle at the parity bar of the other cases."""
+are no multiple of the tile (partial feature tiles), one to four K slices, every epilogue (a down projection in one slice
+adds the residual itself) and K ranges from two stages of the ring up, shorter than the ring that they are loaded into.
+The small shapes' default runs are checked against the oracle at the parity bar of the other cases."""
 import pytest
 import torch
 
 from paper_2507_06608_amd import synth
 
 from tests.parity_util import assert_close, f32, run_oracle
+from tests.test_gpu_parity import EXTRA_SHAPES
 
 pytestmark = pytest.mark.gpu
 
+# K = 64 (two stages of 32) in the QKV and gate/up projections, 128 in the other two
+SMALL = dict(EXTRA_SHAPES, tiny=synth.SHAPES["tiny"], k64=synth.ModelShape("k64", 64, 2, 2, 64, 96, 10000.0))
 TILES = ["128", "128d", "192x128", "256x128", "320x128", "192x256", "256", "320"]
 
 
@@ -28,10 +32,11 @@ def oracle():
     return oracle
 
 
-@pytest.mark.parametrize("shape,chunks", [("tiny", [129]), ("tiny", [200, 133]), ("llama3_8b", [131]), ("qwen25_14b", [300, 77]), ("llama3_8b", [1033])],
-                         ids=["tiny 129", "tiny 333", "8B 131", "14B 377", "8B 1033"])
+@pytest.mark.parametrize("shape,chunks", [("tiny", [129]), ("tiny", [200, 133]), ("llama3_8b", [131]), ("qwen25_14b", [300, 77]), ("llama3_8b", [1033]),
+                                          ("gqa5", [190, 71]), ("gqa8", [300]), ("k64", [150, 61])],
+                         ids=["tiny 129", "tiny 333", "8B 131", "14B 377", "8B 1033", "one down slice, K 736", "one down slice, K 512", "K 64"])
 def test_all_tile_shapes_agree(nx, oracle, monkeypatch, shape, chunks):
-    sh = synth.SHAPES[shape]
+    sh = SMALL[shape] if shape in SMALL else synth.SHAPES[shape]
     wl = synth.make_workload("tiles", sh, 3, chunk_lens=chunks, prefix_lens=[17] * len(chunks), decode_ctx=[], kv_device="cuda:0")
     w = synth.make_weights(sh, 3)
 
@@ -53,7 +58,7 @@ def test_all_tile_shapes_agree(nx, oracle, monkeypatch, shape, chunks):
         return y
 
     y = run(None)
-    if shape == "tiny":
+    if shape in SMALL:
         ref = run_oracle(oracle, wl, w)
         assert_close(f"{shape} {chunks}", f32(y), ref["y_p"])
     for tiles in TILES:
