@@ -81,3 +81,23 @@ def test_a_request_does_not_depend_on_its_neighbours(nx, shape, n):
     short = [j for j in range(n) if lens[j] < 256]
     assert torch.equal(b.run(order=short), b.run(order=short, hint=max(lens) + 1)), "a looser hint"
     b.ctx.close()
+
+
+def test_a_hint_one_short_in_a_fused_batch(nx):
+    """The same for decode requests riding in a chunked-prefill batch."""
+    print("[case] hint one short, fused batch", flush=True)
+    sh = SHAPES["gqa4"]
+    wl = synth.make_workload("fused", sh, 9, chunk_lens=[40], prefix_lens=[5], decode_ctx=[300, 40], kv_device="cuda:0")
+    ctx = nx.Nexus(sh, max_prefill_tokens=42, max_prefill_reqs=3, max_decode_reqs=2, max_positions=301)
+    ctx.load_layer(0, synth.make_weights(sh, 9))
+    ys = []
+    for hint in (300, 301):
+        pb = nx.DevPrefill(synth.fused_single_batch(wl), ctx.device)
+        kv = ctx.make_kv(wl.k_pool, wl.v_pool)
+        torch.cuda.synchronize()
+        ctx.fused_step(pb, 2, hint, kv)
+        ctx.sync()
+        assert torch.isfinite(pb.y.float()).all()
+        ys.append(pb.y.view(torch.int16).clone())
+    assert torch.equal(*ys)
+    ctx.close()
