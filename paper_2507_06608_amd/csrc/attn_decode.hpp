@@ -19,12 +19,15 @@
 
 namespace nexus {
 
-// Wavefronts the spans are dealt to: one per SIMD of the chip, so that all run at once and end together.  A wavefront
+// Wavefronts the spans are dealt to: one per SIMD, so that all run at once and end together.  A wavefront
 // pays a fixed chain of latencies (context lengths, page ids, first pages: 3 us on an idle chip, 7 us in the queue of a
 // loaded one) per stretch of one request's keys; runs of equal length have few of them.  256 requests with contexts up to
 // 8192, 8B shape: a wavefront per 256-key span 815 us, runs 768 (512, 2048 and 4096 of them instead of 1024: 2 to 3 % more);
 // without regard to spans, cut at any pair, runs took 750, but then a request's cuts, and its rounding, follow from its
-// neighbours' contexts.  Three or four pairs in flight per wavefront instead of two gain nothing.
+// neighbours' contexts.  Three or four pairs in flight per wavefront instead of two gain nothing.  The number of runs
+// changes no result, so it follows the CU share: on up to 64 CUs two per SIMD, as many as it holds (four wavefronts do not keep
+// enough in flight for a CU's 50 GB/s).  64 requests up to 4096, steps of two layers, 1024 runs / these: on 96 CUs 712 / 685 us,
+// on 160 538 / 527, on 224 473 / 455; four layers next to a 512-token chunk on 192 CUs 1946 / 1922 (one per SIMD 1944).
 //
 // Spans, in pairs of pages (32 keys).  Where 256 keys hold a context it is one span, and nothing is to be merged.  Otherwise a
 // long span costs balance (a run is longer or shorter by up to one) and parallelism (a batch of few requests has fewer
@@ -57,11 +60,12 @@ inline int decode_max_spans(int n_reqs, int max_ctx) {
 // Keys of a context that a batch with this hint attends to.  The hint is at least every context with its new token; one that
 // is too small (the scheduler states contexts without the new token) costs no keys up to the next multiple of 256.
 inline int decode_ctx_bound(int max_ctx) { return round_up(max_ctx, 256); }
-inline int decode_grid(int n_reqs, int n_kv_heads, int max_ctx) {
+inline int decode_workers(int cus) { return std::min(kDecWorkers, (cus <= 64 ? 8 : 4) * cus); }
+inline int decode_grid(int n_reqs, int n_kv_heads, int max_ctx, int workers) {
     const long seqs = (long)n_reqs * n_kv_heads;
     if (max_ctx <= kDecWholeCtx) return (int)seqs;
     const long runs = (seqs * ((max_ctx + 31) / 32) + kDecMinPairs - 1) / kDecMinPairs;
-    return (int)(runs < kDecWorkers ? runs : kDecWorkers);
+    return (int)(runs < workers ? runs : workers);
 }
 
 struct AttnDecodeArgs {
@@ -69,6 +73,7 @@ struct AttnDecodeArgs {
     const int32_t *ctx_len, *page_table;
     int n_reqs, max_pages, max_ctx;  // max_ctx: decode_ctx_bound of the hint; <= kDecWholeCtx: outputs go straight to `out`
     int max_spans;  // decode_max_spans of max_ctx
+    int workers;    // decode_workers of the CUs it runs on
     const bf16_t *k_pool, *v_pool;
     int n_pages, Hq, Hkv;
     float scale_log2e;
@@ -105,11 +110,11 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
     constexpr int KK = HD / 32;   // k-steps of QK^T
     constexpr int RT = HD / 16;   // 16-row tiles of O^T
     constexpr int BLK = kPage * HD;  // elements per (page, kv head) block
-    // Results of finished spans, written out at the end of the run or when the stage is full (17 KB at most: eight
-    // wavefronts of a CU fit).  A store counts like a load, and the loads behind it are waited for in order: the 256 requests
+    // Results of finished spans, written out at the end of the run or when the stage is full (20 KB, an eighth of a CU's LDS: as
+    // many wavefronts as its registers hold).  A store counts like a load, and the loads behind it are waited for in order: the 256 requests
     // above, in spans of 8 pairs, took 821 us with every result stored between the pairs, 808 staged per request and kv
-    // head, 781 staged per run (731 with the stores left out).
-    constexpr int kStage = 64 / G < 16 ? 64 / G : 16, CPS = G * HD / 8;  // spans, 16-byte chunks of a span
+    // head, 781 staged per run (731 with the stores left out); in spans of 16 pairs a run fits the stage whole (19 spans, 4 heads).
+    constexpr int kStage = 20480 / (G * (2 * HD + 8) + 4), CPS = G * HD / 8;  // spans, 16-byte chunks of a span
     __shared__ uint4 stage_o[kStage * CPS];
     __shared__ float2 stage_ml[kStage * G];
     __shared__ int stage_slot[kStage];
@@ -137,7 +142,7 @@ __global__ __launch_bounds__(64, 2) void attn_decode_kernel(AttnDecodeArgs a) {
         };
         for (int base = 0; base < a.n_reqs; base += 256) total += scan(base);
         total *= a.Hkv;
-        const int per = max(kDecMinPairs, (total + kDecWorkers - 1) / kDecWorkers);
+        const int per = max(kDecMinPairs, (total + a.workers - 1) / a.workers);
         const int run_begin = w * per;
         if (run_begin >= total) return;
         todo = min(per, total - run_begin);

@@ -202,8 +202,10 @@ constexpr int kChipCUs = 256;  // the plan is sized for the whole chip, whatever
 // shape and on how many CUs are busy: `us` holds it for 64, 128, 192 and 256 of them, measured on MI355X as the slope
 // between K = 1024, 4096 and 8192 of grids that fill those CUs once and twice.  `round_us` is what a round of the grid
 // pays on top (pipeline fill, epilogue).  Two 128 x 128 workgroups share a CU: `us` is the time of such a pair, and a lone
-// one takes kLoneTileUs.  Against 340 timings (256 to 1021 tokens, 1 to 4 slices, 192 and 256 CUs) the estimate is off by
-// 7 % in the mean.
+// one takes kLoneTileUs (the pair wins for K up to 1400 or so; the projections of the 8B, 14B and 70B shapes never take
+// it).  Against 340 timings (256 to 1021 tokens, 1 to 4 slices, 192 and 256 CUs) the estimate is off by 7 % in the mean;
+// outside that range it was checked by whole prefill steps against the planner before it, which knew four shapes and sliced
+// 128 x 128 tiles only: 8B shape, 900 to 2304 tokens, 1.04 to 1.22x as fast, 14B, 1021 to 1792, 1.02 to 1.15x, 70B, 1200 to 3072, 1.03x.
 struct TileShape {
     int variant, FS, TS, per_cu;
     double us[4], round_us;
@@ -254,7 +256,8 @@ static const TileShape *choose_tile(int n_ttiles, int n_ftiles, int Kp, int kste
 // pays 0.29 us per MB of them, written and read back (the kernel that sums them reads S slices of fp32 where it would have
 // read one of half); they are charged 0.7, because a step's other phase pays for them too: with two slices of the QKV and
 // four of the down projection instead of one and two, a 512-token prefill step of the 8B shape takes 1179 us against 1242,
-// and the decode phase next to it on 64 CUs, which bounds a mixed step, 2033 to 2063 against 1915 to 2003.  A reduce kernel
+// and the decode phase next to it on 64 CUs, which bounds a mixed step, 2033 to 2063 against 1915 to 2003 (the only mixed step
+// that the charge was set on).  A reduce kernel
 // of its own, where no later kernel sums the slices in passing, adds 5 us.
 static GemmPlan plan_gemm(int T, int n_ftiles, int Kp, bool own_reduce) {
     const int ksteps = Kp / kGemmBK;
@@ -554,7 +557,7 @@ template <int HD>
 static int launch_attn_decode(const PhaseRun &r, const AttnDecodeArgs &a) {
     nexus_ctx *c = r.c;
     const int G = c->m.n_q_heads / c->m.n_kv_heads;
-    dim3 grid(decode_grid(a.n_reqs, c->m.n_kv_heads, a.max_ctx)), mgrid(a.n_reqs * c->m.n_q_heads);
+    dim3 grid(decode_grid(a.n_reqs, c->m.n_kv_heads, a.max_ctx, a.workers)), mgrid(a.n_reqs * c->m.n_q_heads);
 #define NX_DEC_CASE(GG)                                                                           \
     case GG: {                                                                                    \
         {                                                                                         \
@@ -657,7 +660,7 @@ static int run_layer_stage(const PhaseRun &r, int layer, int stage, LayerCarry &
                 d.n_reqs = r.fused_decode, d.max_pages = r.pb->max_pages, d.max_ctx = decode_ctx_bound(r.fused_max_ctx);
                 d.k_pool = k_pool, d.v_pool = v_pool, d.n_pages = r.kv->n_pages, d.Hq = m.n_q_heads, d.Hkv = m.n_kv_heads;
                 d.scale_log2e = scale_log2e, d.part_o = (f16_t *)c->ws[NEXUS_PHASE_DECODE].part_o, d.part_ml = c->ws[NEXUS_PHASE_DECODE].part_ml;
-                d.max_spans = decode_max_spans(d.n_reqs, d.max_ctx);
+                d.max_spans = decode_max_spans(d.n_reqs, d.max_ctx), d.workers = decode_workers(r.cus);
                 d.out = ws.attn, d.lead_cu = r.pb->cu_chunk, d.n_lead = lead, d.out_row0 = r.pb->n_tokens - r.fused_decode;
                 NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, d) : launch_attn_decode<64>(r, d));
             }
@@ -667,7 +670,7 @@ static int run_layer_stage(const PhaseRun &r, int layer, int stage, LayerCarry &
             a.max_pages = r.db->max_pages, a.max_ctx = decode_ctx_bound(r.db->max_ctx);
             a.k_pool = k_pool, a.v_pool = v_pool, a.n_pages = r.kv->n_pages, a.Hq = m.n_q_heads, a.Hkv = m.n_kv_heads;
             a.scale_log2e = scale_log2e, a.part_o = (f16_t *)ws.part_o, a.part_ml = ws.part_ml, a.out = ws.attn;
-            a.max_spans = decode_max_spans(a.n_reqs, a.max_ctx);
+            a.max_spans = decode_max_spans(a.n_reqs, a.max_ctx), a.workers = decode_workers(r.cus);
             NX_TRY(m.head_dim == 128 ? launch_attn_decode<128>(r, a) : launch_attn_decode<64>(r, a));
         }
         return NEXUS_OK;
