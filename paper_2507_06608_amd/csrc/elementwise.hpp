@@ -42,6 +42,7 @@ __device__ __forceinline__ void sum_partial_y8(const RmsPartial &pp, int t, int 
 // flight before the first value is used.  With 256 threads and two to four chunks each, every chunk but the first waited
 // behind the stores of the one before (with the slices of a projection, 23 x 5120: 7.9 -> 5.5 us, 64 x 4096: 6.6 -> 5.3, 128 x
 // 5120: 8.9 -> 6.9, one row of 4096: 5.4 -> 4.4; 1021 x 5120, where bytes count, 19.0 -> 20.6 of a 690 us layer).
+// The wavefront-per-row form below takes over at 1024 rows, a line drawn against the kernel before this one.
 __host__ __device__ __forceinline__ int rmsnorm_threads(int d) { return round_up(d >> 3, 64); }  // d <= 8192
 template <int IN>
 __global__ __launch_bounds__(1024) void rmsnorm_kernel(const void *__restrict__ x, const bf16_t *__restrict__ g,
@@ -332,8 +333,9 @@ __global__ __launch_bounds__(kRopeDecThreads) void rope_append_decode_kernel(Rop
 // The units come in blocks of 32 of one kind.  Grid: x = 4 groups per 32-row tile of the request-aligned query rows (at
 // least the batch's tile count), y = the workgroups that share a group's blocks.  A short batch is bound by the chain of
 // loads in front of its stores: as many workgroups as there are blocks (14 of the 8B shape) walk one block each (45
-// tokens: 6.5 us, 11.3 with eight workgroups of up to three rounds each; 512 tokens and two K slices 10.7, 14.0).  A long batch is bound by the bytes in flight, hence the
-// form without split-K sums, which needs half the registers (8192 tokens: 61 us, 73.7 with the registers of both).
+// tokens: 6.5 us, 11.3 with eight workgroups of up to three rounds each; 512 tokens 10.7 and 14.0 when their projection was in
+// two K slices, 8.7 now that it is in one).  A long batch is bound by the bytes in flight, hence the form without split-K
+// sums, which needs half the registers (8192 tokens: 61 us, 73.7 with the registers of both).
 __host__ __device__ __forceinline__ int rope_unit_blocks(const RopeArgs &a) {
     return ((a.Hq + a.Hkv) * (a.hd >> 4) + 31) / 32 + (a.Hkv * (a.hd >> 3) + 31) / 32;
 }

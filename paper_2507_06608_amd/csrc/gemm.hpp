@@ -232,7 +232,7 @@ __global__ __launch_bounds__(64 * WF * WT) void gemm_dl_kernel(GemmArgs a) {
     constexpr int NP = FS + TS;
     constexpr int UNITS = NP * BKT;
     static_assert(NWL <= NW && UNITS % NWL == 0, "units must divide evenly over the loading wavefronts");
-    static_assert(NST >= 3 && NST <= 6, "ring of 3 or 4 stages (the stage being refilled must differ from the one just published)");
+    static_assert(NST >= 3 && NST <= 6, "ring of 3 to 6 stages (the stage being refilled must differ from the one just published)");
     static_assert(BKT == 2 || BKT == 4, "fragment double-buffer parity needs an even number of k-tiles per stage");
     constexpr int LPW = UNITS / NWL;
     constexpr int STAGE = UNITS * 1024;
