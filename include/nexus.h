@@ -230,7 +230,11 @@ int nexus_retire_cu_splits(nexus_ctx *ctx);
 /* Chunked-prefill phase alone, on the prefill stream of the current layout. */
 int nexus_prefill_chunk(nexus_ctx *ctx, int layer_begin, int layer_end, const nexus_prefill_batch *pb,
                         const nexus_kv_cache *kv);
-/* Decode phase alone, on the decode stream of the current layout. */
+/*
+ * Decode phase alone, on the decode stream of the current layout.  A request's output depends, bit for bit, on its own
+ * input, cache and context and on n_reqs (the order of summation changes at 32, 64 and 128 requests, then every 32): not on
+ * the other requests' contexts, its place in the batch, max_ctx or the CU share.
+ */
 int nexus_decode_step(nexus_ctx *ctx, int layer_begin, int layer_end, const nexus_decode_batch *db,
                       const nexus_kv_cache *kv);
 
