@@ -244,7 +244,7 @@ int nexus_decode_step(nexus_ctx *ctx, int layer_begin, int layer_end, const nexu
  * results; the phase's workspace (activations, split-K partial sums, attention partials) is laid out in a
  * static device array of the library instead of the context's own buffers, so the call performs no hipMalloc /
  * hipFree and calls no allocating routine; a small clear kernel (no memset node) zeroes what must start at zero.
- * The array is 48 MiB per GPU, exists from library load to process exit and is shared by every context on that
+ * The array is 52 MiB per GPU, exists from library load to process exit and is shared by every context on that
  * GPU: calls that overlap in time on one GPU race on it (calls of one context are ordered by the decode stream).
  * A step whose workspace does not fit fails with NEXUS_ESHAPE before anything is launched: the need grows with
  * n_reqs x (the split-K partial sums of the widest split projection + the attention partials of the longest context,
