@@ -13,8 +13,8 @@
 //
 // K/V tiles of 32 keys (2 pages of K, 2 of V) move global->LDS asynchronously (global_load_lds_dwordx4, 1 KiB per
 // wavefront instruction, page blocks copied verbatim) into a ring of stages: the tiles in flight, the tile whose K
-// operands are read, and the two before it, whose V operands are read two iterations later.  The request's page ids
-// are staged in LDS once so that no load waits on a page-table read.  A short chunk has too few (strip, head) pairs
+// operands are read, and the two before it, whose V operands are read two iterations later.  A wavefront keeps the page ids of
+// 64 key tiles in two registers so that no load waits on a page-table read.  A short chunk has too few (strip, head) pairs
 // to fill the chip, so the key range can be split over gridDim.z workgroups whose partial (max, sum, O) results are
 // merged by attn_prefill_merge_kernel; the split count depends on the problem only.
 #pragma once
@@ -22,7 +22,7 @@
 
 namespace nexus {
 
-constexpr int kAttnMaxPages = 2048;  // page ids staged in LDS per workgroup (32K tokens of context)
+constexpr int kAttnMaxPages = 2048;  // longest page table row read (32K tokens of context)
 
 struct AttnPrefillArgs {
     const bf16_t *q;  // P32 [request-aligned rows][Hq*hd]
@@ -54,9 +54,10 @@ constexpr int kAttnTile = 32;   // keys per LDS stage (2 pages of K and of V)
 constexpr float kAttnLazyLog2 = 8.f;  // rise of a row's running maximum (log2 units) that moves the exponents' reference
 // Tiles issued ahead of the one whose K operands are read.  The ring holds those, that one, and the two before it
 // (V operands are read two iterations after the K operands).  A workgroup of up to four wavefronts shares its CU
-// with a second one, and two rings of more than four 16 KiB stages would not fit the CU's LDS next to the staged
-// page ids: it looks one tile ahead.
-constexpr int attn_ahead(int n_waves) { return n_waves > 4 ? 3 : 1; }
+// with a second one: two rings of five 16 KiB stages are all of the CU's LDS.  (With the page ids staged there too it was four
+// stages and one tile ahead, and a tile that came from HBM kept its iteration waiting: five ragged chunks of the 14B shape, steps
+// of four layers, 2642 -> 2618 us, 8192 tokens of the 8B shape, two layers, 6989 -> 6932.)
+constexpr int attn_ahead(int n_waves) { return n_waves > 4 ? 3 : 2; }
 constexpr int attn_stages(int n_waves) { return attn_ahead(n_waves) + 3; }
 
 // Wavefronts per workgroup: the registers allow two per SIMD, eight per CU.  Four to a workgroup and two workgroups per CU
@@ -84,7 +85,6 @@ __global__ __launch_bounds__(64 * attn_waves(G), 2) void attn_prefill_kernel(Att
     constexpr int KK = HD / 16;              // k-steps of the QK^T product
     constexpr int RT = HD / 32;              // 32-row tiles of O^T
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    int32_t *s_pt = (int32_t *)(smem + NST * STAGE);
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave-uniform: branches on it are scalar branches
@@ -132,16 +132,17 @@ __global__ __launch_bounds__(64 * attn_waves(G), 2) void attn_prefill_kernel(Att
             for (int e = 0; e < 8; ++e) qf[kk][e] = (__bf16)0.f;
     }
 
-    // Page ids of the request, staged once.  Ids out of range become page 0: every load then has a valid address
-    // (and every wavefront issues the same number of loads per tile); what such a page delivers is masked out.
-    for (int i = tid; i < pages_valid; i += 64 * NW) {
-        const int page = pt[i];
-        s_pt[i] = (unsigned)page < (unsigned)a.n_pages ? page : 0;
-    }
-    // The query loads above are waited for here, once: inside the loop only the tile loads are then in flight,
-    // and the counted waits on them are the only vector-memory waits the loop needs.
+    // Page ids, one per lane: those of 32 tiles, and of the next 32, fetched while these are in use.  Ids out of range become page 0: every load then has a valid address (and every wavefront issues the same number of
+    // loads per tile); what such a page delivers is masked out.
+    auto page_ids = [&](int tile) {
+        const int lp = 2 * tile + lane;
+        const int id = lp < pages_valid ? pt[lp] : 0;
+        return (unsigned)id < (unsigned)a.n_pages ? id : 0;
+    };
+    int ids = page_ids(t_begin), ids_next = page_ids(t_begin + 32), ids_tile = t_begin;
+    // The query loads above are waited for here, once: inside the loop only the tile loads are then in flight (and a page-id load
+    // every 32 tiles, which can only make a wait longer), and the counted waits on them are the only vector-memory waits the loop needs.
     wait_vmcnt_attn<0>();
-    __syncthreads();
 
     f32x16 o_acc[RT];
 #pragma unroll
@@ -154,9 +155,11 @@ __global__ __launch_bounds__(64 * attn_waves(G), 2) void attn_prefill_kernel(Att
     auto issue = [&](int tile) {
         if (w >= LW) return;
         char *dst = smem + (tile % NST) * STAGE;
-        // the tile's two page ids, read once
-        const int page_a = tile * 2 < pages_valid ? s_pt[tile * 2] : 0;
-        const int page_b = tile * 2 + 1 < pages_valid ? s_pt[tile * 2 + 1] : 0;
+        if (tile - ids_tile == 32) {
+            ids = ids_next, ids_tile = tile;
+            ids_next = page_ids(tile + 32);
+        }
+        const int page_a = __builtin_amdgcn_readlane(ids, 2 * (tile - ids_tile)), page_b = __builtin_amdgcn_readlane(ids, 2 * (tile - ids_tile) + 1);
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
             const int u = w + LW * i;

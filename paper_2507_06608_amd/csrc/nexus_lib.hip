@@ -521,7 +521,7 @@ static int launch_attn_prefill(const PhaseRun &r, const AttnPrefillArgs &base) {
 #define NX_ATTN_CASE(GG)                                                                                             \
     case GG: {                                                                                                       \
         auto kern = attn_prefill_kernel<HD, GG>;                                                                     \
-        constexpr int smem = attn_stages(attn_waves(GG)) * 4 * kPage * HD * 2 + kAttnMaxPages * 4;                         \
+        constexpr int smem = attn_stages(attn_waves(GG)) * 4 * kPage * HD * 2;                         \
         static bool done = false;                                                                                    \
         if (!done) {                                                                                                 \
             HIP_TRY(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));      \
