@@ -71,3 +71,32 @@ def test_an_unknown_tile_shape_is_refused(nx, monkeypatch):
     monkeypatch.setenv("NEXUS_GEMM_TILES", "128x129")
     with pytest.raises(nx.NexusError, match="128x129"):
         nx.Nexus(synth.SHAPES["tiny"], max_prefill_tokens=256, max_prefill_reqs=1, max_decode_reqs=1, max_positions=256)
+
+
+@pytest.mark.parametrize("shape,chunks,tiles", [("tiny", [129], "256"), ("tiny", [200, 133], "192x128"), ("llama3_8b", [512], "320"), ("qwen25_14b", [300, 77], "192x128"),
+                                                ("qwen25_14b", [700], "256"), ("llama3_8b", [700], "320x128")],
+                         ids=["fewer tiles than XCDs", "tiny 333", "180 tiles", "81 tiles", "324 tiles", "two K slices"])
+def test_grids_that_are_no_multiple_of_the_xcds(nx, monkeypatch, shape, chunks, tiles):
+    """On a share of the chip such a grid is dealt to the XCDs in ranges, on the whole chip it runs in launch order: every
+    tile is computed once in both, with the same bits."""
+    print(f"[case] ragged grid {shape} {chunks} {tiles}", flush=True)
+    monkeypatch.setenv("NEXUS_GEMM_TILES", tiles)
+    sh = synth.SHAPES[shape]
+    wl = synth.make_workload("ragged", sh, 5, chunk_lens=chunks, prefix_lens=[9] * len(chunks), decode_ctx=[], kv_device="cuda:0")
+    ctx = nx.context_for(wl)
+    ctx.load_layer(0, synth.make_weights(sh, 5))
+    kv = ctx.make_kv(wl.k_pool, wl.v_pool)
+    pb = nx.DevPrefill(wl.prefill, ctx.device)
+    out = []
+    for split in (None, (192, 64), (96, 160)):
+        if split:
+            ctx.set_cu_split(*split)
+        pb.y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        ctx.prefill_chunk(pb, kv)
+        ctx.sync()
+        out.append(pb.y.clone())
+    ctx.close()
+    assert torch.isfinite(out[0].float()).all()
+    for y in out[1:]:
+        assert torch.equal(y.view(torch.int16), out[0].view(torch.int16))
