@@ -14,6 +14,7 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "gemm_plan.hpp"
 
 namespace nexus {
 
@@ -42,8 +43,6 @@ struct GemmArgs {
     int n_xcd;             // XCDs the tiles are dealt to in contiguous ranges; 1: tile order = launch order
     int group_f;           // feature blocks per tile group (tile-order remap inside an XCD), >= 1
 };
-
-constexpr int kGemmBK = 64;  // unit of the split-K bookkeeping: ksteps_per_split counts 64-wide k steps
 
 __device__ __forceinline__ float silu_f(float z) { return z / (1.0f + __expf(-z)); }
 
