@@ -244,8 +244,9 @@ int nexus_decode_step(nexus_ctx *ctx, int layer_begin, int layer_end, const nexu
  * results; the phase's workspace (activations, split-K partial sums, attention partials) is laid out in a
  * static device array of the library instead of the context's own buffers, so the call performs no hipMalloc /
  * hipFree and calls no allocating routine; a small clear kernel (no memset node) zeroes what must start at zero.
- * The array is 52 MiB per GPU, exists from library load to process exit and is shared by every context on that
- * GPU: calls that overlap in time on one GPU race on it (calls of one context are ordered by the decode stream).
+ * The array is 76 MiB per GPU (of which a step of more than 128 requests may take 52), exists from library load to process
+ * exit and is shared by every context on that GPU: calls that overlap in time on one GPU race on it (calls of one
+ * context are ordered by the decode stream).
  * A step whose workspace does not fit fails with NEXUS_ESHAPE before anything is launched: the need grows with
  * n_reqs x (the split-K partial sums of the widest split projection + the attention partials of the longest context,
  * one per 256 keys and query head; per 512 beyond 4096 keys in batches of more than 64, per 64 or 128 up to 4096 keys in

@@ -90,11 +90,13 @@ inline const TileShape *choose_tile(int n_ttiles, int n_ftiles, int Kp, int kste
 }
 
 // Depends on the problem only (never on the CU share): S fixes the summation order, so results are bit-identical
-// across layouts.  Up to 128 tokens K is cut into as many slices (8 at most) as leave at most one workgroup per CU: a second
-// workgroup on some of the CUs makes the others wait for those, as it is the bytes a CU has to load that count.  (Slices used
-// to be doubled until there were 192 workgroups: right for the 8B shape but for its QKV, while the 40 feature blocks of the 14B
-// shape's O and down projections became 320 workgroups.  23 rows, 8 -> 6 slices: O 13.0 -> 10.5 us, down 28.6 -> 22.7;
-// 128 rows 18.3 -> 15.8, 34.3 -> 31.7; QKV of the 8B shape, 64 rows, 4 -> 5 slices 12.5 -> 11.7.)  Beyond 128 tokens S is the one with the least estimated time of GEMM and partial sums.  By itself a phase
+// across layouts.  Up to 128 tokens K is cut along until there are 192 workgroups, by doubling: on any share a CU that gets one
+// workgroup more than another then has little more to load, as it is the bytes a CU has to load that count.  (As many slices as
+// leave at most one workgroup per CU of the whole chip, six for the 40 feature blocks of the 14B shape's O and down projections
+// instead of eight, is faster there and slower on most shares, where S is the same: steps of three layers of the 14B shape, 64 / 128
+// requests, eight -> six slices: 256 CUs 481 -> 447 us / 594 -> 583, 224 CUs 475 -> 491 / 601 -> 656, 192 590 -> 611 / 745 -> 800,
+// 160 589 -> 613 / 748 -> 812, 128 637 -> 617 / 845 -> 795, 96 827 -> 818 / 1047 -> 1081, 32 1635 -> 1634 / 2218 -> 2347.)
+// Beyond 128 tokens S is the one with the least estimated time of GEMM and partial sums.  By itself a phase
 // pays 0.29 us per MB of them, written and read back (the kernel that sums them reads S slices of fp32 where it would have
 // read one of half); they are charged 0.7, because a step's other phase pays for them too: with two slices of the QKV and
 // four of the down projection instead of one and two, a 512-token prefill step of the 8B shape takes 1179 us against 1242,
@@ -113,7 +115,7 @@ inline GemmPlan plan_gemm(int T, int n_ftiles, int Kp, bool own_reduce) {
         else if (T <= 64) p.variant = GV_S64, p.TS = 2;
         else p.variant = GV_S128, p.TS = 4;
         const int blocks = ((n_ftiles + p.FS - 1) / p.FS) * ((nt + p.TS - 1) / p.TS);
-        S = std::max(1, std::min(8, kChipCUs / blocks));
+        while (S < 8 && blocks * S < (3 * kChipCUs) / 4) S *= 2;
         while (S > 1 && ksteps / S < min_ksteps) --S;
     } else {
         double best = 0.0;

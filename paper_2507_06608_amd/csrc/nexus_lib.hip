@@ -39,7 +39,10 @@ using namespace nexus;
 // Workspace of nexus_decode_step_noalloc: device memory that exists from the moment the library is loaded, so the
 // call allocates nothing.  One copy per GPU, shared by every context on that GPU, held until the process ends.  In
 // host code the array's name is only a handle: its device address comes from hipGetSymbolAddress, once per device.
-constexpr size_t kScratchBytes = (size_t)52 << 20;
+// A step may take 52 MiB of it, up to 128 requests all 76: K of their projections was once cut into fewer slices (see plan_gemm), with
+// which a step fitted 52 MiB, and none of their partial sums have grown by more than 23.9 MiB since (128 rows, 191 feature blocks, two
+// slices instead of none; the largest step among 60 million that fitted then needs 71.1 MiB now).
+constexpr size_t kScratchBytes = (size_t)76 << 20, kScratchBytesOver128 = (size_t)52 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 static unsigned char *g_scratch_ptr[kMaxDevices] = {};
@@ -1166,9 +1169,10 @@ int nexus_decode_step_noalloc(nexus_ctx *c, int lb, int le, const nexus_decode_b
     PhaseWs ws;
     size_t zero_bytes = 0;
     const size_t need = carve_decode_ws(c, db->n_reqs, db->max_ctx, le - lb > 1, nullptr, nullptr, &zero_bytes);
-    if (need > kScratchBytes)
+    const size_t limit = db->n_reqs <= 128 ? kScratchBytes : kScratchBytesOver128;
+    if (need > limit)
         return fail(NEXUS_ESHAPE, "a decode step of %d requests with contexts up to %d needs %zu bytes of workspace, the static scratch array holds %zu",
-                    db->n_reqs, db->max_ctx, need, kScratchBytes);
+                    db->n_reqs, db->max_ctx, need, limit);
     DeviceGuard dg(c->device);
     NX_TRY(debug_validate(c, nullptr, db, kv));
     unsigned char *base = nullptr;

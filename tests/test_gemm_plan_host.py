@@ -1,0 +1,48 @@
+"""Rules of the GEMM planner (csrc/gemm_plan.hpp), compiled with a host compiler: no GPU involved."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2507_06608_amd import synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+SHARES = range(32, 257, 32)
+MODELS = ("llama3_8b", "qwen25_14b", "llama3_70b")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "gemm_plan")
+    r = subprocess.run(["g++", "-std=c++17", "-Wall", "-Werror", "-o", exe, os.path.join(ROOT, "tests", "gemm_plan_driver.cpp")], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-4000:]
+
+    def run(lines):
+        r = subprocess.run([exe], input="".join(l + "\n" for l in lines), capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        out = [tuple(int(x) for x in l.split()) for l in r.stdout.splitlines()]
+        assert len(out) == len(lines)
+        return out
+    return run
+
+
+def projections(s):
+    """(features, K, own reduction) of a layer's four projections."""
+    return [(s.n_qkv, s.hidden, 0), (s.hidden, s.q_dim, 0), (2 * s.ffn, s.hidden, 1), (s.hidden, s.ffn, 0)]
+
+
+@pytest.mark.parametrize("shape", MODELS)
+def test_slices_up_to_128_rows_suit_every_share(ask, shape):
+    """The number of K slices cannot follow the CU share (it is the order of summation), so it has to suit all of them: the CU that
+    loads most loads at most 1.8 times its part of a split projection (2 slots of a CU for w workgroups on c CUs are 2 c / w times; the
+    grids of these shapes reach 1.75, and 240 workgroups, which suit 256 CUs best, are 1.87 on 224 and up to 8 % of a step)."""
+    projs = projections(synth.SHAPES[shape])
+    rows = [1, 23, 32, 33, 64, 65, 128]
+    plans = ask([f"plan {t} {n // 32} {k} {own}" for t in rows for n, k, own in projs])
+    for i, (s, _, fs, ts) in enumerate(plans):
+        n, t = projs[i % 4][0], rows[i // 4]
+        blocks = -(-(n // 32) // fs) * -(-(-(-t // 32)) // ts)
+        assert s == 1 or blocks * s >= 192 or s == 8, (t, n, s)
+        for c in SHARES:
+            if s > 1:
+                assert -(-blocks * s // c) * c <= 1.8 * blocks * s, (t, n, s, c)

@@ -129,3 +129,25 @@ def test_noalloc_decode_step_takes_what_fits(nx):
     assert torch.isfinite(outs[1].float()).all()
     assert torch.equal(_bits(outs[0]), _bits(outs[1]))
     ctx.close()
+
+
+def test_noalloc_decode_step_takes_a_full_pool_of_long_contexts_whatever_the_slices(nx):
+    """128 requests of 9728 keys at the 14B shape need 57 MiB with the O and down projections in eight K slices; with six they
+    fitted 52 MiB, and what fitted then has to fit still."""
+    print("[case] no-alloc decode step, 128 requests of 9728 keys", flush=True)
+    sh = synth.SHAPES["qwen25_14b"]
+    wl = synth.make_workload("fits too", sh, 26, chunk_lens=[], prefix_lens=[], decode_ctx=[9727] * 128, kv_device="cuda:0")
+    ctx = nx.context_for(wl)
+    ctx.load_layer(0, synth.make_weights(sh, 26))
+    kv = ctx.make_kv(wl.k_pool, wl.v_pool)
+    outs = []
+    for call in (ctx.decode_step, ctx.decode_step_noalloc):
+        db = nx.DevDecode(wl.decode, ctx.device)
+        db.y.fill_(float("nan"))
+        torch.cuda.synchronize()
+        call(db, kv)
+        ctx.sync()
+        outs.append(db.y.clone())
+    assert torch.isfinite(outs[1].float()).all()
+    assert torch.equal(_bits(outs[0]), _bits(outs[1]))
+    ctx.close()
