@@ -40,7 +40,7 @@ struct GemmArgs {
     int out_Kp;
     float *partial;        // [S][T][N]
     int n_tblk;            // token blocks in the grid
-    int n_xcd;             // XCDs the tiles are dealt to in contiguous ranges; 1: tile order = launch order
+    int n_xcd;             // XCDs the tiles are dealt to in contiguous ranges (tile_xcds); 1: tile order = launch order
     int group_f;           // feature blocks per tile group (tile-order remap inside an XCD), >= 1
 };
 
@@ -246,14 +246,8 @@ __global__ __launch_bounds__(64 * WF * WT) void gemm_dl_kernel(GemmArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wf = w % WF, wt = w / WF;
-    int nblk = gridDim.x, bid = blockIdx.x;
-    // Workgroups are dealt to the XCDs round-robin: give every XCD a contiguous range of tiles (the first nblk % n_xcd of the
-    // ranges are one longer; another K slice starts at another XCD, which renames the ranges and no more), ...
-    if (a.n_xcd > 1) {
-        const int x = bid % a.n_xcd;
-        bid = x * (nblk / a.n_xcd) + min(x, nblk % a.n_xcd) + bid / a.n_xcd;
-    }
-    // ... and walk that range in groups of group_f feature blocks, feature block fastest: the tiles resident on an
+    const int nblk = gridDim.x, bid = tile_of_block(blockIdx.x, nblk, a.n_xcd);
+    // Every XCD walks its range of tiles in groups of group_f feature blocks, feature block fastest: the tiles resident on an
     // XCD at one time then form a group_f x (residents / group_f) rectangle, whose operands (group_f weight blocks +
     // the rectangle's token blocks) are fetched into that XCD's L2 once instead of once per tile.
     int tb, fb;

@@ -3,6 +3,12 @@
 #include <algorithm>
 #include <cstddef>
 
+#if defined(__HIPCC__)
+#define NEXUS_HOST_DEVICE __host__ __device__ __forceinline__
+#else
+#define NEXUS_HOST_DEVICE inline
+#endif
+
 namespace nexus {
 
 constexpr int kGemmBK = 64;  // unit of the split-K bookkeeping: ksteps_per_split counts 64-wide k steps
@@ -133,6 +139,29 @@ inline GemmPlan plan_gemm(int T, int n_ftiles, int Kp, bool own_reduce) {
         p.variant = t->variant, p.FS = t->FS, p.TS = t->TS;
     }
     return p;
+}
+
+// Tile of a workgroup.  Workgroups are dealt to the XCDs round-robin: every XCD gets a contiguous range of the n tiles, the first
+// n % n_xcd of the ranges one longer; n_xcd = 1: launch order.  (Another K slice starts at another XCD if n is no multiple of them,
+// which renames the ranges and no more.)
+NEXUS_HOST_DEVICE int tile_of_block(int block, int n, int n_xcd) {
+    if (n_xcd <= 1) return block;
+    const int x = block % n_xcd, longer = n % n_xcd;
+    return x * (n / n_xcd) + (x < longer ? x : longer) + block / n_xcd;
+}
+// XCDs that a grid of n tiles a K slice is dealt to in ranges (1: launch order).  A multiple of the XCDs always is.  Another one is on
+// a share of the chip only, and there only if there are two blocks of tokens, K is in one slice and the grid fits the share's CUs:
+// in launch order the two workgroups of a block of weights then run at one time on different XCDs, both fetch the weights, and the
+// phase next to it, bound by its own reads, pays for that too.  Kernel times, ranges against launch order (8B, 14B and 70B shapes,
+// 160 to 1500 tokens, shares of 64 to 240 CUs): 34 such grids are 1.04 times as fast next to a decode phase (0.99 to 1.17; 1.00 on
+// 112 CUs and fewer) and 1.02 times by themselves (0.97 to 1.11); four layers of the 8B shape, 512 tokens on 192 CUs next to 64 decode
+// requests on 64, 2029 -> 1983 us, on another card 1941 -> 1917.  The other grids, next to a decode phase and by themselves: three
+// and more blocks of tokens 0.99 (0.87 to 1.08) and 0.99 (0.93 to 1.06), two in more than one round 0.98 (0.95 to 1.02) and 0.99
+// (0.96 to 1.01), two in several slices 1.01 (0.93 to 1.12) and 1.00 (0.96 to 1.06), one 1.00 and 1.00.  On the whole chip 54 grids
+// of 22 to 540 tiles: 0.99 (0.94 to 1.06).
+inline int tile_xcds(int n, int n_tblk, int S, int cus, int n_cus, int n_xcd) {
+    const bool pairs = cus < n_cus && n_tblk == 2 && S == 1 && n <= cus;
+    return n % n_xcd == 0 || pairs ? n_xcd : 1;
 }
 
 }  // namespace nexus

@@ -328,12 +328,7 @@ static int run_gemm(const PhaseRun &r, int kernel_id, const f16_t *W, int N_pack
     a.group_f = 4;
     const int n_fblk = (n_ftiles + FS - 1) / FS;
     dim3 grid(a.n_tblk * n_fblk, 1, p.S);
-    // A grid that is no multiple of the XCDs: on a share of the chip the ranges, for the other phase's sake, which pays for the
-    // weight blocks that two XCDs fetch instead of one (180 tiles of gate/up, 512 tokens of the 8B shape on 192 CUs next to 64
-    // decode requests on 64: steps of four layers 2029 -> 1983 us, 1941 -> 1917 on another card).  By itself such a GEMM is as
-    // fast or a few per cent faster in launch order (54 grids of 22 to 540 tiles, 160 to 1500 tokens, whole chip: 0.94 to 1.06
-    // times as fast with the ranges, 0.99 in the mean): workgroups that share fewer operands do not wait for the same lines.
-    a.n_xcd = grid.x % r.n_xcd == 0 || r.cus < c->n_cus ? r.n_xcd : 1;
+    a.n_xcd = tile_xcds((int)grid.x, a.n_tblk, p.S, r.cus, c->n_cus, r.n_xcd);
     if (p.S > kMaxSlices) return fail(NEXUS_ESTATE, "internal: %d split-K slices, the reductions unroll over %d", p.S, kMaxSlices);
     if (p.S > 1 && (size_t)p.S * r.T * N_packed > ws.partial_elems)
         return fail(NEXUS_ESTATE, "split-K workspace too small (%d x %d x %d)", p.S, r.T, N_packed);

@@ -46,3 +46,17 @@ def test_slices_up_to_128_rows_suit_every_share(ask, shape):
         for c in SHARES:
             if s > 1:
                 assert -(-blocks * s // c) * c <= 1.8 * blocks * s, (t, n, s, c)
+
+
+# tiles, blocks of tokens, slices, CUs of the share, dealt in ranges?  Of the grids whose kernels were timed in both orders.
+ORDERS = [(180, 2, 1, 192, True), (174, 2, 1, 176, True), (180, 2, 1, 208, True),      # faster in ranges: one round of two blocks of tokens
+          (180, 2, 1, 96, False), (300, 2, 1, 160, False),                             # two rounds
+          (270, 3, 1, 160, False), (261, 3, 1, 96, False), (540, 3, 1, 192, False), (52, 4, 4, 224, False),  # three and four blocks
+          (52, 2, 3, 160, False), (44, 2, 2, 96, False),                               # several slices
+          (180, 2, 1, 256, False), (22, 1, 4, 96, False),                              # the whole chip; one block
+          (176, 2, 1, 192, True), (256, 3, 2, 256, True), (8, 1, 1, 64, True)]         # multiples of the XCDs
+
+
+@pytest.mark.parametrize("tiles,n_tblk,slices,cus,ranges", ORDERS, ids=[f"{o[0]} tiles, {o[1]} blocks, {o[2]} slices, {o[3]} CUs" for o in ORDERS])
+def test_which_grids_are_dealt_in_ranges(ask, tiles, n_tblk, slices, cus, ranges):
+    assert ask([f"xcds {tiles} {n_tblk} {slices} {cus}"]) == [(8 if ranges else 1,)]
