@@ -60,3 +60,14 @@ ORDERS = [(180, 2, 1, 192, True), (174, 2, 1, 176, True), (180, 2, 1, 208, True)
 @pytest.mark.parametrize("tiles,n_tblk,slices,cus,ranges", ORDERS, ids=[f"{o[0]} tiles, {o[1]} blocks, {o[2]} slices, {o[3]} CUs" for o in ORDERS])
 def test_which_grids_are_dealt_in_ranges(ask, tiles, n_tblk, slices, cus, ranges):
     assert ask([f"xcds {tiles} {n_tblk} {slices} {cus}"]) == [(8 if ranges else 1,)]
+
+
+def test_every_tile_is_computed_once(ask):
+    """tile_of_block, which the kernel calls, is a permutation of the tiles for any grid and number of XCDs, and an XCD's workgroups
+    (they are dealt round-robin) hold one contiguous range of tiles."""
+    grids = [(n, x) for x in (1, 2, 7, 8) for n in list(range(1, 600)) + [4096, 4099]]
+    for (n, x), order in zip(grids, ask([f"order {n} {x} 0 0" for n, x in grids])):
+        assert sorted(order) == list(range(n)), (n, x)
+        for d in range(x):
+            mine = order[d::x]
+            assert x == 1 or list(mine) == list(range(mine[0], mine[0] + len(mine))) if mine else True, (n, x, d)

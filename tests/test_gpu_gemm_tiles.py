@@ -73,29 +73,39 @@ def test_an_unknown_tile_shape_is_refused(nx, monkeypatch):
         nx.Nexus(synth.SHAPES["tiny"], max_prefill_tokens=256, max_prefill_reqs=1, max_decode_reqs=1, max_positions=256)
 
 
-@pytest.mark.parametrize("shape,chunks,tiles", [("tiny", [129], "256"), ("tiny", [200, 133], "192x128"), ("llama3_8b", [512], "320"), ("qwen25_14b", [300, 77], "192x128"),
+# Tiles and blocks of tokens of the projections, with K in one slice but for some of the down projections.  Two blocks of tokens in
+# one slice are dealt in ranges on 192 CUs, the others run in launch order everywhere.
+@pytest.mark.parametrize("shape,chunks,tiles", [("tiny", [200, 133], "256"), ("tiny", [257], "320"), ("llama3_8b", [512], "320"), ("qwen25_14b", [257], "320"),
+                                                ("qwen25_14b", [129], "320x128"), ("tiny", [129], "256"), ("tiny", [200, 133], "192x128"), ("qwen25_14b", [300, 77], "192x128"),
                                                 ("qwen25_14b", [700], "256"), ("llama3_8b", [700], "320x128")],
-                         ids=["fewer tiles than XCDs", "tiny 333", "180 tiles", "81 tiles", "324 tiles", "two K slices"])
+                         ids=["12, 4 and 22 tiles of two blocks", "10, 4 and 18 of two", "180 of two", "174 of two", "174 of two, 128 tokens", "6, 2 and 11 of one block",
+                              "24, 9 and 45 of three", "three blocks", "84, 60 and 324 of three", "six blocks, three slices"])
 def test_grids_that_are_no_multiple_of_the_xcds(nx, monkeypatch, shape, chunks, tiles):
-    """On a share of the chip such a grid is dealt to the XCDs in ranges, on the whole chip it runs in launch order: every
-    tile is computed once in both, with the same bits."""
+    """In either order every tile is computed, with the same bits on the whole chip and on shares.  Another chunk runs through the
+    context before each run, so that what a left-out tile would leave behind is wrong (the workspace keeps every intermediate)."""
     print(f"[case] ragged grid {shape} {chunks} {tiles}", flush=True)
     monkeypatch.setenv("NEXUS_GEMM_TILES", tiles)
     sh = synth.SHAPES[shape]
-    wl = synth.make_workload("ragged", sh, 5, chunk_lens=chunks, prefix_lens=[9] * len(chunks), decode_ctx=[], kv_device="cuda:0")
+    wl, other = (synth.make_workload("ragged", sh, seed, chunk_lens=chunks, prefix_lens=[9] * len(chunks), decode_ctx=[], kv_device="cuda:0") for seed in (5, 6))
     ctx = nx.context_for(wl)
     ctx.load_layer(0, synth.make_weights(sh, 5))
-    kv = ctx.make_kv(wl.k_pool, wl.v_pool)
-    pb = nx.DevPrefill(wl.prefill, ctx.device)
-    out = []
-    for split in (None, (192, 64), (96, 160)):
-        if split:
-            ctx.set_cu_split(*split)
-        pb.y.fill_(float("nan"))
+    kv, kv_other = ctx.make_kv(wl.k_pool, wl.v_pool), ctx.make_kv(other.k_pool, other.v_pool)
+    pb, pb_other = nx.DevPrefill(wl.prefill, ctx.device), nx.DevPrefill(other.prefill, ctx.device)
+
+    def run(split, batch, pools):
+        ctx.set_cu_split(*split)
+        batch.y.fill_(float("nan"))
         torch.cuda.synchronize()
-        ctx.prefill_chunk(pb, kv)
+        ctx.prefill_chunk(batch, pools)
         ctx.sync()
-        out.append(pb.y.clone())
+        return batch.y.clone()
+
+    whole = (nx.CUS_ALL, nx.CUS_ALL)
+    out = []
+    for split in (whole, (192, 64), (96, 160)):
+        before = run(whole, pb_other, kv_other)
+        out.append(run(split, pb, kv))
+        assert not torch.isclose(before.float(), out[-1].float()).all(dim=1).any(), "the other chunk has to leave other values"
     ctx.close()
     assert torch.isfinite(out[0].float()).all()
     for y in out[1:]:
