@@ -14,7 +14,7 @@
 // K/V tiles of 32 keys (2 pages of K, 2 of V) move global->LDS asynchronously (global_load_lds_dwordx4, 1 KiB per
 // wavefront instruction, page blocks copied verbatim) into a ring of stages: the tiles in flight, the tile whose K
 // operands are read, and the two before it, whose V operands are read two iterations later.  A wavefront keeps the page ids of
-// 64 key tiles in two registers so that no load waits on a page-table read.  A short chunk has too few (strip, head) pairs
+// 64 key tiles in two registers, so that a load waits on a page-table read once in 32 tiles.  A short chunk has too few (strip, head) pairs
 // to fill the chip, so the key range can be split over gridDim.z workgroups whose partial (max, sum, O) results are
 // merged by attn_prefill_merge_kernel; the split count depends on the problem only.
 #pragma once
@@ -55,8 +55,9 @@ constexpr float kAttnLazyLog2 = 8.f;  // rise of a row's running maximum (log2 u
 // Tiles issued ahead of the one whose K operands are read.  The ring holds those, that one, and the two before it
 // (V operands are read two iterations after the K operands).  A workgroup of up to four wavefronts shares its CU
 // with a second one: two rings of five 16 KiB stages are all of the CU's LDS.  (With the page ids staged there too it was four
-// stages and one tile ahead, and a tile that came from HBM kept its iteration waiting: five ragged chunks of the 14B shape, steps
-// of four layers, 2642 -> 2618 us, 8192 tokens of the 8B shape, two layers, 6989 -> 6932.)
+// stages and one tile ahead, and a tile that came from HBM kept its iteration waiting.  This kernel's time, two cards: five ragged
+// chunks of the 14B shape over up to 4000 keys 91 -> 88 and 90 -> 86 us, four of 2048 tokens of the 8B shape over up to 6144 596 -> 573
+// and 587 -> 565, 1021 tokens over 5000 on 160 CUs 165 -> 155 and 160 -> 149; a whole prefill step 0 to 2 % less.)
 constexpr int attn_ahead(int n_waves) { return n_waves > 4 ? 3 : 2; }
 constexpr int attn_stages(int n_waves) { return attn_ahead(n_waves) + 3; }
 
@@ -132,16 +133,21 @@ __global__ __launch_bounds__(64 * attn_waves(G), 2) void attn_prefill_kernel(Att
             for (int e = 0; e < 8; ++e) qf[kk][e] = (__bf16)0.f;
     }
 
-    // Page ids, one per lane: those of 32 tiles, and of the next 32, fetched while these are in use.  Ids out of range become page 0: every load then has a valid address (and every wavefront issues the same number of
-    // loads per tile); what such a page delivers is masked out.
+    // Page ids, one per lane: those of 32 tiles, and of the next 32.  Ids out of range become page 0: every load then has a valid
+    // address (and every wavefront issues the same number of loads per tile); what such a page delivers is masked out.
+    // The check uses the ids as soon as they are read, so a wavefront waits, once in 32 tiles, for its loads in flight and this read.
+    // Kept as they were read and checked when their turn comes the read is not waited for, but the loads in flight still are;
+    // this kernel's time with the ids in LDS / as here / checked later / in one register, read when needed: four chunks of 2048 tokens of
+    // the 8B shape 587 / 565 / 573 / 574 us, five ragged chunks of the 14B shape 89.9 / 85.9 / 85.6 / 86.6, 2048 tokens of the 70B
+    // shape 252 / 245 / 247 / 248.
     auto page_ids = [&](int tile) {
         const int lp = 2 * tile + lane;
         const int id = lp < pages_valid ? pt[lp] : 0;
         return (unsigned)id < (unsigned)a.n_pages ? id : 0;
     };
     int ids = page_ids(t_begin), ids_next = page_ids(t_begin + 32), ids_tile = t_begin;
-    // The query loads above are waited for here, once: inside the loop only the tile loads are then in flight (and a page-id load
-    // every 32 tiles, which can only make a wait longer), and the counted waits on them are the only vector-memory waits the loop needs.
+    // The query loads above are waited for here, once: inside the loop only the tile loads are then in flight, and the counted
+    // waits on them, with the page-id read's own every 32 tiles, are the only vector-memory waits the loop needs.
     wait_vmcnt_attn<0>();
 
     f32x16 o_acc[RT];
@@ -368,7 +374,7 @@ __global__ __launch_bounds__(64 * attn_waves(G), 2) void attn_prefill_kernel(Att
             u32x4 vf[2][RT];
             read_v(smem + ((tile - 2) % NST) * STAGE, vf);
             read_k(smem + (tile % NST) * STAGE, kf);
-            // the refill (page ids out of LDS, addresses, loads) comes behind the operand reads: it works tiles ahead
+            // the refill (page ids out of a register, addresses, loads) comes behind the operand reads: it works tiles ahead
             // and is in no hurry, the matrix unit waits for the operands
             tile_refill(tile);
             rescale(alpha_pend);
