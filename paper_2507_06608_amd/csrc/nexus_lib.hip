@@ -305,14 +305,16 @@ static int run_gemm(const PhaseRun &r, int kernel_id, const f16_t *W, int N_pack
             t = choose_tile(a.n_ttiles, n_ftiles, Kp, p.ksteps_per_split, p.S, r.cus);
         variant = t->variant, FS = t->FS, TS = t->TS;
     }
-    // Measured on 64 of the 256 CUs (T = 64): gate/up 113 -> 98 us, down 55 -> 48, O 21.6 -> 18.9 with the wide
-    // variant, QKV (too few workgroups left) 27 -> 30; on 96 CUs and more the narrow one wins or ties.
+    // 33..64 tokens on at most 64 CUs, where the wide grid still gives 7 of 8 CUs two workgroups.  64 rows, narrow -> wide, us: 8B shape on
+    // 64 CUs gate/up 107 -> 93, down 57 -> 50, O 23 -> 22 (QKV, 96 wide workgroups, stays narrow: 27 -> 30), 14B QKV 44 -> 40, O 33 -> 35,
+    // down 68 -> 70, 70B QKV 78 -> 82, gate/up 365 -> 371, O 62 -> 56, down 197 -> 170; on 32 CUs all of them but the 14B shape's
+    // QKV gain 2 to 16 %; on 96 CUs and more the narrow one wins or ties.
     if (variant == GV_S64 && r.cus <= 64 && (long)((n_ftiles + 7) / 8) * p.S >= 2L * r.cus - r.cus / 4) variant = GV_S64W, FS = 8;
-    // 65..128 tokens, measured on config 4's decode batch (128 tokens) on 256 / 96 CUs, 128-feature against 256-feature
-    // workgroups: QKV 23 / 44 us against 29 / 46, gate/up 62 / 132 against 80 / 137, O 24 / 37 against 21 / 32, down
-    // 45 / 73 against 36 / 61 (the 128 x 128-tile kernel this replaces: 26 / 48, 74 / 147, 23 / 32, 49 / 71).  The
-    // wide workgroup wins where the narrow grid would be far more workgroups than the chip has CUs (the deeply split
-    // O and down projections); the rule looks at the problem only.
+    // 65..128 tokens: the wide workgroup where the narrow grid would be far more workgroups than the chip has CUs (the rule looks at the
+    // problem only): O and down of the 14B shape (320), QKV and gate/up of the 70B shape (320, 448).  128 rows, narrow -> wide, us on 256 /
+    // 192 / 128 / 96 / 32 CUs: 14B O 24 -> 22 / 24 -> 21 / 30 -> 32 / 37 -> 32 / 83 -> 68, down 44 -> 38 / 44 -> 37 / 58 -> 61 / 73 -> 61 /
+    // 167 -> 135, 70B QKV 54 -> 47 / 53 -> 45 / 68 -> 71 / 82 -> 69 / 189 -> 153, gate/up 180 -> 154 / 237 -> 231 / 293 -> 250 / 340 -> 329 /
+    // 886 -> 705.  Below the line the narrow one: 14B QKV (224) 23 -> 29 on 256 CUs and 44 -> 46 on 96, gate/up (216) 62 -> 80 and 132 -> 137.
     if (variant == GV_S128 && (long)((n_ftiles + 3) / 4) * p.S > kChipCUs + kChipCUs / 8) variant = GV_S128W, FS = 8;
     const int last_ksteps = Kp / kGemmBK - (p.S - 1) * p.ksteps_per_split;  // the shortest k range of the grid
     if (last_ksteps < kStreamDepth)
