@@ -96,12 +96,13 @@ inline const TileShape *choose_tile(int n_ttiles, int n_ftiles, int Kp, int kste
 }
 
 // Depends on the problem only (never on the CU share): S fixes the summation order, so results are bit-identical
-// across layouts.  Up to 128 tokens K is cut along until there are 192 workgroups, by doubling: on any share a CU that gets one
-// workgroup more than another then has little more to load, as it is the bytes a CU has to load that count.  (As many slices as
-// leave at most one workgroup per CU of the whole chip, six for the 40 feature blocks of the 14B shape's O and down projections
-// instead of eight, is faster there and slower on most shares, where S is the same: steps of three layers of the 14B shape, 64 / 128
-// requests, eight -> six slices: 256 CUs 481 -> 447 us / 594 -> 583, 224 CUs 475 -> 491 / 601 -> 656, 192 590 -> 611 / 745 -> 800,
-// 160 589 -> 613 / 748 -> 812, 128 637 -> 617 / 845 -> 795, 96 827 -> 818 / 1047 -> 1081, 32 1635 -> 1634 / 2218 -> 2347.)
+// across layouts.  Up to 128 tokens the slices are doubled until there are 192 workgroups: it is the bytes that the most loaded CU has
+// to load that count, and with the projections of the 8B, 14B and 70B shapes that is at most 1.75 times its part on any share.  (As
+// many slices as leave at most one workgroup per CU of the whole chip, six for the 40 feature blocks of the 14B shape's O and down
+// projections instead of eight, are faster there and slower on most shares, where S has to be the same; beyond 64 rows they also miss
+// the wide workgroups, see run_gemm.  Steps of three layers of the 14B shape, 64 / 128 requests, eight -> six slices: 256 CUs 481 -> 447
+// us / 594 -> 583, 224 CUs 475 -> 491 / 601 -> 656, 192 590 -> 611 / 745 -> 800, 160 589 -> 613 / 748 -> 812, 128 637 -> 617 / 845 -> 795,
+// 96 827 -> 818 / 1047 -> 1081, 32 1635 -> 1634 / 2218 -> 2347.)
 // Beyond 128 tokens S is the one with the least estimated time of GEMM and partial sums.  By itself a phase
 // pays 0.29 us per MB of them, written and read back (the kernel that sums them reads S slices of fp32 where it would have
 // read one of half); they are charged 0.7, because a step's other phase pays for them too: with two slices of the QKV and
@@ -150,17 +151,17 @@ NEXUS_HOST_DEVICE int tile_of_block(int block, int n, int n_xcd) {
     return x * (n / n_xcd) + (x < longer ? x : longer) + block / n_xcd;
 }
 // XCDs that a grid of n tiles a K slice is dealt to in ranges (1: launch order).  A multiple of the XCDs always is.  Another one is on
-// a share of the chip only, and there only if there are two blocks of tokens, K is in one slice and the grid fits the share's CUs:
-// in launch order the two workgroups of a block of weights then run at one time on different XCDs, both fetch the weights, and the
-// phase next to it, bound by its own reads, pays for that too.  Kernel times, ranges against launch order (8B, 14B and 70B shapes,
-// 160 to 1500 tokens, shares of 64 to 240 CUs): 34 such grids are 1.04 times as fast next to a decode phase (0.99 to 1.17; 1.00 on
-// 112 CUs and fewer) and 1.02 times by themselves (0.97 to 1.11); four layers of the 8B shape, 512 tokens on 192 CUs next to 64 decode
-// requests on 64, 2029 -> 1983 us, on another card 1941 -> 1917.  The other grids, next to a decode phase and by themselves: three
-// and more blocks of tokens 0.99 (0.87 to 1.08) and 0.99 (0.93 to 1.06), two in more than one round 0.98 (0.95 to 1.02) and 0.99
-// (0.96 to 1.01), two in several slices 1.01 (0.93 to 1.12) and 1.00 (0.96 to 1.06), one 1.00 and 1.00.  On the whole chip 54 grids
-// of 22 to 540 tiles: 0.99 (0.94 to 1.06).
+// a share of the chip only, and there only if there are two blocks of tokens and all slices fit the share's CUs, more than half of the
+// chip: in launch order the two workgroups of a block of weights then run at one time on different XCDs, both fetch the weights, and
+// the phase next to it, bound by its own reads, pays for that too.  Kernel times, ranges against launch order (8B, 14B and 70B shapes,
+// 160 to 1500 tokens): such grids on shares of 144 to 240 CUs are 1.04 times as fast next to a decode phase in the median if K is in
+// one slice (40 timings, 1.01 to 1.17) and 1.01 in several (125, 0.93 to 1.11), and 1.02 (0.97 to 1.06) and 1.00 (0.96 to 1.06) by
+// themselves; four layers of the 8B shape, 512 tokens on 192 CUs next to 64 decode requests on 64, 2029 -> 1983 us, on another card
+// 1941 -> 1917.  The other grids, next to a decode phase and by themselves: two blocks of tokens on 96 CUs 0.99 and 0.99, in more than
+// one round 0.98 (0.95 to 1.02) and 0.99 (0.96 to 1.01), three and more blocks 1.00 (0.87 to 1.08) and 0.99 (0.93 to 1.06), one 1.00 and
+// 1.00.  On the whole chip 54 grids of 22 to 540 tiles: 0.99 (0.94 to 1.06).
 inline int tile_xcds(int n, int n_tblk, int S, int cus, int n_cus, int n_xcd) {
-    const bool pairs = cus < n_cus && n_tblk == 2 && S == 1 && n <= cus;
+    const bool pairs = cus < n_cus && 2 * cus > n_cus && n_tblk == 2 && n * S <= cus;
     return n % n_xcd == 0 || pairs ? n_xcd : 1;
 }
 

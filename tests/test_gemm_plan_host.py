@@ -49,12 +49,12 @@ def test_slices_up_to_128_rows_suit_every_share(ask, shape):
 
 
 # tiles, blocks of tokens, slices, CUs of the share, dealt in ranges?  Of the grids whose kernels were timed in both orders.
-ORDERS = [(180, 2, 1, 192, True), (174, 2, 1, 176, True), (180, 2, 1, 208, True),      # faster in ranges: one round of two blocks of tokens
-          (180, 2, 1, 96, False), (300, 2, 1, 160, False),                             # two rounds
-          (270, 3, 1, 160, False), (261, 3, 1, 96, False), (540, 3, 1, 192, False), (52, 4, 4, 224, False),  # three and four blocks
-          (52, 2, 3, 160, False), (44, 2, 2, 96, False),                               # several slices
-          (180, 2, 1, 256, False), (22, 1, 4, 96, False),                              # the whole chip; one block
-          (176, 2, 1, 192, True), (256, 3, 2, 256, True), (8, 1, 1, 64, True)]         # multiples of the XCDs
+ORDERS = [(180, 2, 1, 192, True), (174, 2, 1, 176, True), (180, 2, 1, 208, True), (44, 2, 4, 176, True), (86, 2, 2, 176, True),  # faster in ranges
+          (180, 2, 1, 176, False), (300, 2, 1, 160, False), (44, 2, 4, 168, False),              # more than one round
+          (86, 2, 1, 96, False), (44, 2, 2, 96, False), (46, 2, 2, 128, False),                  # half of the chip and less
+          (270, 3, 1, 160, False), (135, 5, 1, 192, False), (540, 3, 1, 192, False), (52, 4, 4, 224, False),  # three and more blocks of tokens
+          (180, 2, 1, 256, False), (22, 1, 4, 96, False), (150, 1, 1, 160, False),               # the whole chip; one block
+          (176, 2, 1, 192, True), (256, 3, 2, 256, True), (8, 1, 1, 64, True)]                   # multiples of the XCDs
 
 
 @pytest.mark.parametrize("tiles,n_tblk,slices,cus,ranges", ORDERS, ids=[f"{o[0]} tiles, {o[1]} blocks, {o[2]} slices, {o[3]} CUs" for o in ORDERS])

@@ -73,8 +73,8 @@ def test_an_unknown_tile_shape_is_refused(nx, monkeypatch):
         nx.Nexus(synth.SHAPES["tiny"], max_prefill_tokens=256, max_prefill_reqs=1, max_decode_reqs=1, max_positions=256)
 
 
-# Tiles and blocks of tokens of the projections, with K in one slice but for some of the down projections.  Two blocks of tokens in
-# one slice are dealt in ranges on 192 CUs, the others run in launch order everywhere.
+# Tiles and blocks of tokens of the projections.  Two blocks of tokens that fit 192 CUs, slices and all, are dealt in ranges there; the
+# others run in launch order everywhere.
 @pytest.mark.parametrize("shape,chunks,tiles", [("tiny", [200, 133], "256"), ("tiny", [257], "320"), ("llama3_8b", [512], "320"), ("qwen25_14b", [257], "320"),
                                                 ("qwen25_14b", [129], "320x128"), ("tiny", [129], "256"), ("tiny", [200, 133], "192x128"), ("qwen25_14b", [300, 77], "192x128"),
                                                 ("qwen25_14b", [700], "256"), ("llama3_8b", [700], "320x128")],
